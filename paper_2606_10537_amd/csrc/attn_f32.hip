@@ -1,94 +1,260 @@
 // fp32 attention kernels (stage a prefill, Eq. 5 first sum, stage c decode).
 //
-// On MI355X the fp32 matrix-core peak equals the fp32 vector peak, so the fp32
-// path runs on plain VALU FMAs: one thread owns one query row (q and the
-// running output in registers), K/V tiles of 32 rows are staged in LDS and read
-// by broadcast.  Probabilities stay fp32 throughout.
+// The products run on v_mfma_f32_16x16x4_f32 (fp32 operands, products and sums):
+// 256 FLOP per clock and CU, twice what unpacked VALU FMAs reach, and a wave's
+// operands fit its registers.  (One thread per query row with q and the output
+// row in registers, the layout before, spilled at d = 128 and left most CUs
+// idle: 964 us for a 16-head decode of 72 x 499 rows, 125 us for the prefill of
+// four chunks of 177 rows, d = 64.)
+//
+// fp32 calls are small, so what counts is the depth of one workgroup: its waves
+// share 16 QB query rows and split the keys, 32 at a time and wave; every wave
+// keeps its own online softmax, and the partial rows are merged through LDS at
+// the end, in a fixed order.  No key is read by two waves of a workgroup, so K and
+// V go from memory straight to registers: the next K block while this one's
+// softmax and P*V run, the next V block during the next S.  QB = 2 halves the
+// K/V traffic per product and is taken when it still fills the CUs; QB = 1 with
+// twice the waves otherwise.
+//
+// Operand layouts of 16x16x4 (lane q = lane % 16, g = lane / 16): A holds row q,
+// B column q, both at k = g; element r of the result is row 4 g + r of column q.
+//   S^T = K Q^T: four k steps share one 16-byte read of either operand: step e of
+//     group s takes d = 16 s + 4 g + e.  The result is keys 4 g + r of query q.
+//   O^T += V^T P^T: step r takes keys 4 g + r, so P^T is the result of S^T as it
+//     stands.  The A rows of d block (c, e) are d = 64 c + 4 q + e: one 16-byte
+//     read of a V row serves four blocks, and o[4 c + e][r] is d = 64 c + 16 g +
+//     4 r + e, four neighbours over e.
 #include "pd_common.h"
 #include "pd_kernels.h"
 
 namespace pd {
 
-constexpr int kF32Rows = 64;   // query rows per workgroup (one wave)
-constexpr int kF32Keys = 32;   // keys per LDS tile
+constexpr int kF32Table = 512;   // key rows whose addresses are resident at a time
 
 __device__ __forceinline__ f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+__device__ __forceinline__ f32x4 mfma16x16x4(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
 
-template <int D>
-struct RowState {
-  float q[D], o[D];
-  float m, l, qmass;
+// Lanes q, q + 16, q + 32, q + 48 hold the same query.
+__device__ __forceinline__ float max_over_groups(float x) {
+  x = fmaxf(x, __shfl_xor(x, 16));
+  return fmaxf(x, __shfl_xor(x, 32));
+}
+__device__ __forceinline__ float sum_over_groups(float x) {
+  x += __shfl_xor(x, 16);
+  return x + __shfl_xor(x, 32);
+}
+
+template <int D, int QB, int NW>
+struct F32Lds {
+  static constexpr int R = 16 * QB, P = D + 4;   // rows of a workgroup; padded row of partial outputs
+  const float *k[kF32Table], *v[kF32Table];
+  float o[NW][R][P];
+  float m[NW][R], l[NW][R], mass[NW][R];
 };
 
-template <int D>
-__device__ __forceinline__ void row_init(RowState<D>& st, const float* src) {
+// Attention of the workgroup's R query rows over keys [j0, j1).  qrow(i) is the
+// pointer of row i or NULL (zeros), key(j, k, v) gives the K and V rows of key j,
+// range(i, lo, hi) the keys whose mass is counted for row i (MASS).  Then
+// out(i, d, x) receives four merged, normalised output values of row i from d on
+// and row(i, m, l, mass) its log2-domain maximum, weight sum and mass.
+template <int D, int QB, int NW, bool MASS, class QRow, class Key, class Range, class Out, class Row>
+__device__ __forceinline__ void attend_f32(F32Lds<D, QB, NW>& lds, int j0, int j1, float scale_log2, QRow&& qrow,
+                                           Key&& key, Range&& range, Out&& out, Row&& row) {
+  constexpr int KS = D / 16, DC = D / 64, R = 16 * QB;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q = lane & 15, g = lane >> 4;
+  f32x4 qf[QB][KS], o[QB][4 * DC];
+  float m[QB], l[QB], mass[QB];
+  int lo[QB], hi[QB];
 #pragma unroll
-  for (int i = 0; i < D; i += 4) {
-    f32x4 v = src ? ld4(src + i) : f32x4{0.f, 0.f, 0.f, 0.f};
-    st.q[i] = v[0]; st.q[i + 1] = v[1]; st.q[i + 2] = v[2]; st.q[i + 3] = v[3];
+  for (int b = 0; b < QB; ++b) {
+    const float* src = qrow(16 * b + q);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) qf[b][s] = src ? ld4(src + 16 * s + 4 * g) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 4 * DC; ++i) o[b][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    m[b] = -INFINITY;
+    l[b] = mass[b] = 0.f;
+    if constexpr (MASS) range(16 * b + q, lo[b], hi[b]);
   }
+  for (int c0 = j0; c0 < j1; c0 += kF32Table) {
+    const int nk = min(kF32Table, j1 - c0);
+    if (c0 > j0) __syncthreads();   // the previous addresses are no longer read
+    for (int i = tid; i < kF32Table; i += 64 * NW) {
+      const float *kp = nullptr, *vp = nullptr;
+      if (i < nk) key(c0 + i, kp, vp);
+      lds.k[i] = kp;
+      lds.v[i] = vp;
+    }
+    __syncthreads();
+    // 32 keys i0 .. i0+31 of the table; rows past the end have no address and are zero.
+    f32x4 kf[2][KS], vf[2][4][DC];
+    auto load_k = [&](int i0) {
 #pragma unroll
-  for (int i = 0; i < D; ++i) st.o[i] = 0.f;
-  st.m = -INFINITY;
-  st.l = 0.f;
-  st.qmass = 0.f;
-}
-
-// One LDS tile of `nk` valid keys; keys [qlo, qhi) (tile-relative) add to qmass.
-template <int D>
-__device__ __forceinline__ void row_tile(RowState<D>& st, const float (*Ks)[D], const float (*Vs)[D], int nk,
-                                         float scale_log2, int qlo, int qhi) {
-  float s[kF32Keys];
-  float mt = -INFINITY;
+      for (int h = 0; h < 2; ++h) {
+        const float* p = lds.k[i0 + 16 * h + q];
 #pragma unroll
-  for (int kk = 0; kk < kF32Keys; ++kk) {
-    float acc = 0.f;
+        for (int s = 0; s < KS; ++s) kf[h][s] = p ? ld4(p + 16 * s + 4 * g) : f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    };
+    auto load_v = [&](int i0) {
 #pragma unroll
-    for (int i = 0; i < D; ++i) acc = fmaf(st.q[i], Ks[kk][i], acc);
-    s[kk] = kk < nk ? acc * scale_log2 : -INFINITY;
-    mt = fmaxf(mt, s[kk]);
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float* p = lds.v[i0 + 16 * h + 4 * g + r];
+#pragma unroll
+          for (int c = 0; c < DC; ++c) vf[h][r][c] = p ? ld4(p + 64 * c + 4 * q) : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    int i0 = 32 * wave;
+    if (i0 < nk) {
+      load_k(i0);
+      load_v(i0);
+    }
+    for (; i0 < nk; i0 += 32 * NW) {
+      f32x4 s[2][QB];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int b = 0; b < QB; ++b) s[h][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int b = 0; b < QB; ++b) s[h][b] = mfma16x16x4(kf[h][ks][e], qf[b][ks][e], s[h][b]);
+      const int next = i0 + 32 * NW;
+      if (next < nk) load_k(next);
+#pragma unroll
+      for (int b = 0; b < QB; ++b) {
+        float mt = -INFINITY;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            s[h][b][r] = i0 + 16 * h + 4 * g + r < nk ? s[h][b][r] * scale_log2 : -INFINITY;
+            mt = fmaxf(mt, s[h][b][r]);
+          }
+        mt = max_over_groups(mt);
+        if (__ballot(mt > m[b])) {
+          const float mn = fmaxf(m[b], mt), a = fast_exp2(m[b] - mn);
+          m[b] = mn;
+          l[b] *= a;
+          mass[b] *= a;
+#pragma unroll
+          for (int i = 0; i < 4 * DC; ++i) o[b][i] *= a;
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float p = fast_exp2(s[h][b][r] - m[b]);
+            s[h][b][r] = p;
+            l[b] += p;
+            if constexpr (MASS) {
+              const int j = c0 + i0 + 16 * h + 4 * g + r;
+              mass[b] += j >= lo[b] && j < hi[b] ? p : 0.f;
+            }
+          }
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int c = 0; c < DC; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+              for (int b = 0; b < QB; ++b) o[b][4 * c + e] = mfma16x16x4(vf[h][r][c][e], s[h][b][r], o[b][4 * c + e]);
+      if (next < nk) load_v(next);
+    }
   }
-  if (mt > st.m) {
-    const float a = fast_exp2(st.m - mt);
-    st.m = mt;
-    st.l *= a;
-    st.qmass *= a;
+  // Merge the waves' partial rows: O = sum_w 2^(m_w - M) O_w / sum_w 2^(m_w - M) l_w.
 #pragma unroll
-    for (int i = 0; i < D; ++i) st.o[i] *= a;
+  for (int b = 0; b < QB; ++b) {
+    const int i = 16 * b + q;
+    const float lt = sum_over_groups(l[b]), mst = sum_over_groups(mass[b]);
+    if (g == 0) {
+      lds.m[wave][i] = m[b];
+      lds.l[wave][i] = lt;
+      lds.mass[wave][i] = mst;
+    }
+#pragma unroll
+    for (int c = 0; c < DC; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        *reinterpret_cast<f32x4*>(&lds.o[wave][i][64 * c + 16 * g + 4 * r]) =
+            f32x4{o[b][4 * c][r], o[b][4 * c + 1][r], o[b][4 * c + 2][r], o[b][4 * c + 3][r]};
   }
+  __syncthreads();
+  for (int u = tid; u < R * (D / 4); u += 64 * NW) {
+    const int i = u / (D / 4), d = 4 * (u % (D / 4));
+    float M = -INFINITY;
 #pragma unroll
-  for (int kk = 0; kk < kF32Keys; ++kk) {
-    const float pv = fast_exp2(s[kk] - st.m);
-    st.l += pv;
-    if (kk >= qlo && kk < qhi) st.qmass += pv;
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, lds.m[w][i]);
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    float L = 0.f, ms = 0.f;
 #pragma unroll
-    for (int i = 0; i < D; ++i) st.o[i] = fmaf(pv, Vs[kk][i], st.o[i]);
-  }
-}
-
-template <int D>
-__device__ __forceinline__ void row_store(float* dst, const RowState<D>& st, float inv) {
-#pragma unroll
-  for (int i = 0; i < D; i += 4) {
-    f32x4 v = {st.o[i] * inv, st.o[i + 1] * inv, st.o[i + 2] * inv, st.o[i + 3] * inv};
-    *reinterpret_cast<f32x4*>(dst + i) = v;
+    for (int w = 0; w < NW; ++w) {
+      // A wave without keys has m = -inf and zeros: weight 0, whatever M is.
+      const float a = lds.l[w][i] == 0.f ? 0.f : fast_exp2(lds.m[w][i] - M);
+      acc += a * *reinterpret_cast<const f32x4*>(&lds.o[w][i][d]);
+      L += a * lds.l[w][i];
+      ms += a * lds.mass[w][i];
+    }
+    out(i, d, acc * (1.0f / L));
+    if (d == 0) row(i, M, L, ms);
   }
 }
 
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(64) void prefill_f32_kernel(PrefillArgs p) {
-  __shared__ __attribute__((aligned(16))) float Ks[kF32Keys][D];
-  __shared__ __attribute__((aligned(16))) float Vs[kF32Keys][D];
+// Prefill.  Workgroups [0, total): (b, n, h, tile of 16 QB rows).  The others,
+// one per (b, n, kv head): the chunk's cache rows and, summed in a fixed order,
+// its key mean.
+template <int D, int QB, int NW>
+__global__ __launch_bounds__(64 * NW) void prefill_f32_kernel(PrefillArgs p, float* key_mean) {
+  __shared__ __attribute__((aligned(16))) F32Lds<D, QB, NW> lds;
   const float* q_pre = reinterpret_cast<const float*>(p.q_pre);
   const float* k_pre = reinterpret_cast<const float*>(p.k_pre);
   const float* v_pre = reinterpret_cast<const float*>(p.v_pre);
+  const int C1 = p.C + 1, tid = threadIdx.x;
+  if ((int)blockIdx.x >= p.total) {
+    constexpr int CH = D / 4, NG = 64 * NW / CH;   // 16-byte chunks of a row; rows in flight
+    const size_t bng = blockIdx.x - p.total, chunk = bng / p.Hkv;
+    const int g = (int)(bng % p.Hkv), c = tid % CH, rg = tid / CH;
+    float* kc = reinterpret_cast<float*>(p.k_cache) + bng * C1 * D + 4 * c;
+    float* vc = reinterpret_cast<float*>(p.v_cache) + bng * C1 * D + 4 * c;
+    const size_t src = (chunk * C1 * p.Hkv + g) * D + 4 * c;
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int r = rg; r < C1; r += NG) {
+      const size_t at = src + (size_t)r * p.Hkv * D;
+      const f32x4 k = ld4(k_pre + at);
+      *reinterpret_cast<f32x4*>(kc + (size_t)r * D) = k;
+      *reinterpret_cast<f32x4*>(vc + (size_t)r * D) = ld4(v_pre + at);
+      if (r >= 1) sum += k;   // content rows only
+    }
+    *reinterpret_cast<f32x4*>(&lds.o[0][0][0] + rg * D + 4 * c) = sum;
+    static_assert(NG * D <= NW * 16 * QB * (D + 4), "partial sums fit");
+    __syncthreads();
+    if (tid < D) {
+      float s = 0.f;
+      for (int r = 0; r < NG; ++r) s += (&lds.o[0][0][0])[r * D + tid];
+      key_mean[bng * D + tid] = s * (1.0f / p.C);
+    }
+    return;
+  }
   const float* q_qm = reinterpret_cast<const float*>(p.q_qm);
   const float* k_qm = reinterpret_cast<const float*>(p.k_qm);
   const float* v_qm = reinterpret_cast<const float*>(p.v_qm);
   float* o = reinterpret_cast<float*>(p.o);
-
-  int lid = blockIdx.x;
+  int lid = xcd_remap(blockIdx.x, p.total);
   const int rb = lid % p.n_qt;
   lid /= p.n_qt;
   const int h = lid % p.Hq;
@@ -96,119 +262,105 @@ __global__ __launch_bounds__(64) void prefill_f32_kernel(PrefillArgs p) {
   const int n = lid % p.N;
   const int b = lid / p.N;
   const int g = h / p.G;
-  const int C1 = p.C + 1;
   const size_t chunk = (size_t)b * p.N + n;
   const size_t qm_base = (p.qm_per_chunk ? chunk : (size_t)b) * (size_t)(p.Lq + p.Lm);
-  const int tid = threadIdx.x;
-  const int row = rb * kF32Rows + tid;
-
-  RowState<D> st;
-  const float* qsrc = nullptr;
-  if (row < C1) qsrc = q_pre + ((chunk * C1 + row) * p.Hq + h) * D;
-  else if (row < p.Sc) qsrc = q_qm + ((qm_base + (row - C1)) * p.Hq + h) * D;
-  row_init<D>(st, qsrc);
-
-  // Keys counted into qmass: the query columns for the BOS and content rows
-  // (second sum of Eq. 5), the content columns for the query and pseudo-label
-  // rows when the chunk score is asked for.
-  const int qc_lo = C1, qc_hi = C1 + p.Lq;
-  const int m_lo = row < C1 ? qc_lo : 1;
-  const int m_hi = row < C1 ? qc_hi : (p.qm_mass ? C1 : 1);
-  const int ntile = (p.Sc + kF32Keys - 1) / kF32Keys;
-  constexpr int CPR = D / 4;
-  for (int t = 0; t < ntile; ++t) {
-    for (int i = tid; i < kF32Keys * CPR; i += kF32Rows) {
-      const int kk = i / CPR, c = i % CPR;
-      const int r = t * kF32Keys + kk;
-      f32x4 kv = {0.f, 0.f, 0.f, 0.f}, vv = kv;
-      if (r < C1) {
-        const size_t off = ((chunk * C1 + r) * p.Hkv + g) * D + 4 * c;
-        kv = ld4(k_pre + off);
-        vv = ld4(v_pre + off);
-      } else if (r < p.Sc) {
-        const size_t off = ((qm_base + (r - C1)) * p.Hkv + g) * D + 4 * c;
-        kv = ld4(k_qm + off);
-        vv = ld4(v_qm + off);
-      }
-      *reinterpret_cast<f32x4*>(&Ks[kk][4 * c]) = kv;
-      *reinterpret_cast<f32x4*>(&Vs[kk][4 * c]) = vv;
-    }
-    __syncthreads();
-    const int t0 = t * kF32Keys;
-    row_tile<D>(st, Ks, Vs, min(kF32Keys, p.Sc - t0), p.scale_log2, m_lo - t0, m_hi - t0);
-    __syncthreads();
-  }
-  if (row >= p.Sc) return;
-  const float inv = 1.0f / st.l;
-  row_store<D>(o + ((chunk * p.Sc + row) * p.Hq + h) * D, st, inv);
   const size_t hb = chunk * p.Hq + h;
-  if (row >= 1 && row < C1) p.part_i[hb * p.C + (row - 1)] = st.qmass * inv;
-  if (row >= qc_lo && row < qc_hi) p.lse_q[hb * p.Lq + (row - qc_lo)] = st.m + __log2f(st.l);
-  if (p.qm_mass && row >= C1) p.qm_mass[hb * (p.Lq + p.Lm) + (row - C1)] = st.qmass * inv;
+  const int row0 = rb * 16 * QB;
+  const int qc_lo = C1, qc_hi = C1 + p.Lq;
+  attend_f32<D, QB, NW, true>(
+      lds, 0, p.Sc, p.scale_log2,
+      [&](int i) -> const float* {
+        const int row = row0 + i;
+        if (row < C1) return q_pre + ((chunk * C1 + row) * p.Hq + h) * D;
+        return row < p.Sc ? q_qm + ((qm_base + (row - C1)) * p.Hq + h) * D : nullptr;
+      },
+      [&](int j, const float*& k, const float*& v) {
+        const bool own = j < C1;
+        const size_t at = own ? ((chunk * C1 + j) * p.Hkv + g) * D : ((qm_base + (j - C1)) * p.Hkv + g) * D;
+        k = (own ? k_pre : k_qm) + at;
+        v = (own ? v_pre : v_qm) + at;
+      },
+      // The query columns for the BOS and content rows (second sum of Eq. 5), the content columns for the
+      // query and pseudo-label rows when the chunk score is asked for.
+      [&](int i, int& lo, int& hi) {
+        lo = row0 + i < C1 ? qc_lo : 1;
+        hi = row0 + i < C1 ? qc_hi : (p.qm_mass ? C1 : 1);
+      },
+      [&](int i, int d, f32x4 x) {
+        if (row0 + i < p.Sc) *reinterpret_cast<f32x4*>(o + ((chunk * p.Sc + row0 + i) * p.Hq + h) * D + d) = x;
+      },
+      [&](int i, float m, float l, float mass) {
+        const int row = row0 + i;
+        if (row >= p.Sc) return;
+        if (row >= 1 && row < C1) p.part_i[hb * p.C + (row - 1)] = mass * (1.0f / l);
+        if (row >= qc_lo && row < qc_hi) p.lse_q[hb * p.Lq + (row - qc_lo)] = m + __log2f(l);
+        if (p.qm_mass && row >= C1) p.qm_mass[hb * (p.Lq + p.Lm) + (row - C1)] = mass * (1.0f / l);
+      });
 }
 
 // ---------------------------------------------------------------------------
+// Eq. 5, first sum: one wave per (b, n, h, 16 content keys).  S = Q_q K_c^T with
+// the query rows as A (16 per step) and the keys as B, so a lane holds one key and
+// four query rows; each key's mass exp2(S*scale - lse2(row)) is summed over the
+// rows and added to the head's second sum (or replaces it for the query-to-chunk
+// score); head_sum_rank_kernel sums the heads.
 template <int D>
 __global__ __launch_bounds__(64) void escore_f32_kernel(EscoreArgs p) {
-  __shared__ __attribute__((aligned(16))) float Qs[kF32Keys][D];
-  __shared__ float Ls[kF32Keys];
+  constexpr int KS = D / 16;
   const float* q_qm = reinterpret_cast<const float*>(p.q_qm);
   const float* k_cache = reinterpret_cast<const float*>(p.k_cache);
-  int lid = blockIdx.x;
-  const int cb = lid % p.n_cb;
-  lid /= p.n_cb;
-  const int n = lid % p.N;
-  const int b = lid / p.N;
-  const int C1 = p.C + 1;
-  const size_t chunk = (size_t)b * p.N + n;
-  const size_t qm_base = (p.qm_per_chunk ? chunk : (size_t)b) * (size_t)(p.Lq + p.Lm);
-  const int tid = threadIdx.x;
-  const int j = cb * kF32Rows + tid;
-  constexpr int CPR = D / 4;
-
+  const int lane = threadIdx.x, q = lane & 15, g = lane >> 4;
+  const size_t bnh = blockIdx.x / p.n_cb;   // (b * N + n) * Hq + h
+  const int cb = blockIdx.x % p.n_cb, h = (int)(bnh % p.Hq);
+  const size_t bn = bnh / p.Hq;
+  const int b = (int)(bn / p.N);
+  const size_t qm_base = (p.qm_per_chunk ? bn : (size_t)b) * (size_t)(p.Lq + p.Lm);
+  const float* lse = p.lse_q + bnh * p.Lq;
+  const int j = cb * 16 + q;
+  const float* kp = j < p.C ? k_cache + ((bn * p.Hkv + h / p.G) * (p.C + 1) + 1 + j) * D : nullptr;
+  f32x4 kf[KS], qa[KS], qn[KS];
+#pragma unroll
+  for (int s = 0; s < KS; ++s) kf[s] = kp ? ld4(kp + 16 * s + 4 * g) : f32x4{0.f, 0.f, 0.f, 0.f};
+  float ln[4], lc[4];
+  auto load = [&](int r0, f32x4 (&x)[KS], float (&le)[4]) {
+    const float* src = r0 + q < p.Lq ? q_qm + ((qm_base + r0 + q) * p.Hq + h) * D : nullptr;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) x[s] = src ? ld4(src + 16 * s + 4 * g) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) le[r] = r0 + 4 * g + r < p.Lq ? lse[r0 + 4 * g + r] : INFINITY;
+  };
+  load(0, qn, ln);
   float acc = 0.f;
-  for (int h = 0; h < p.Hq; ++h) {
-    const int g = h / p.G;
-    float kr[D];
-    const float* ksrc = j < p.C ? k_cache + ((chunk * p.Hkv + g) * C1 + 1 + j) * D : nullptr;
+  for (int r0 = 0; r0 < p.Lq; r0 += 16) {
 #pragma unroll
-    for (int i = 0; i < D; i += 4) {
-      f32x4 v = ksrc ? ld4(ksrc + i) : f32x4{0.f, 0.f, 0.f, 0.f};
-      kr[i] = v[0]; kr[i + 1] = v[1]; kr[i + 2] = v[2]; kr[i + 3] = v[3];
-    }
-    const float* lse = p.lse_q + (chunk * p.Hq + h) * p.Lq;
-    for (int q0 = 0; q0 < p.Lq; q0 += kF32Keys) {
-      for (int i = tid; i < kF32Keys * CPR; i += kF32Rows) {
-        const int kk = i / CPR, c = i % CPR;
-        const int r = q0 + kk;
-        f32x4 v = {0.f, 0.f, 0.f, 0.f};
-        if (r < p.Lq) v = ld4(q_qm + ((qm_base + r) * p.Hq + h) * D + 4 * c);
-        *reinterpret_cast<f32x4*>(&Qs[kk][4 * c]) = v;
-      }
-      if (tid < kF32Keys) Ls[tid] = q0 + tid < p.Lq ? lse[q0 + tid] : INFINITY;
-      __syncthreads();
-      for (int kk = 0; kk < kF32Keys; ++kk) {
-        float s = 0.f;
+    for (int s = 0; s < KS; ++s) qa[s] = qn[s];
 #pragma unroll
-        for (int i = 0; i < D; ++i) s = fmaf(Qs[kk][i], kr[i], s);
-        acc += fast_exp2(s * p.scale_log2 - Ls[kk]);
+    for (int r = 0; r < 4; ++r) lc[r] = ln[r];
+    if (r0 + 16 < p.Lq) load(r0 + 16, qn, ln);
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;   // two chains
+#pragma unroll
+    for (int s = 0; s < KS; s += 2)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        s0 = mfma16x16x4(qa[s][e], kf[s][e], s0);
+        s1 = mfma16x16x4(qa[s + 1][e], kf[s + 1][e], s1);
       }
-      __syncthreads();
-    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc += fast_exp2((s0[r] + s1[r]) * p.scale_log2 - lc[r]);
   }
-  if (j < p.C) {
-    float e = 0.f;
-    if (!p.q2c)
-      for (int h = 0; h < p.Hq; ++h) e += p.part_i[(chunk * p.Hq + h) * p.C + j];
-    p.tok_score[chunk * p.C + j] = e + acc;
-  }
+  acc = sum_over_groups(acc);
+  float* ph = p.part_io + bnh * p.C;
+  if (g == 0 && j < p.C) ph[j] = p.q2c ? acc : ph[j] + acc;
 }
 
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(64) void decode_f32_kernel(DecodeArgs p) {
-  __shared__ __attribute__((aligned(16))) float Ks[kF32Keys][D];
-  __shared__ __attribute__((aligned(16))) float Vs[kF32Keys][D];
+// Decode.  Workgroup = (b, kv head, tile of 16 QB of the group's G L_d query
+// rows, KV shard); query row rho of the group is head g*G + rho / L_d, decode row
+// rho % L_d.  Shards are cut at multiples of 32 keys.
+template <int D, int QB, int NW>
+__global__ __launch_bounds__(64 * NW) void decode_f32_kernel(DecodeArgs p) {
+  __shared__ __attribute__((aligned(16))) F32Lds<D, QB, NW> lds;
+  __shared__ int bad_index;   // checking build: some kept row of this shard was out of range
   const float* q_dec = reinterpret_cast<const float*>(p.q_dec);
   const float* k_dec = reinterpret_cast<const float*>(p.k_dec);
   const float* v_dec = reinterpret_cast<const float*>(p.v_dec);
@@ -217,106 +369,126 @@ __global__ __launch_bounds__(64) void decode_f32_kernel(DecodeArgs p) {
   const float* k_static = reinterpret_cast<const float*>(p.k_static);
   const float* v_static = reinterpret_cast<const float*>(p.v_static);
 
-  int lid = blockIdx.x;
+  int lid = xcd_remap(blockIdx.x, p.total);
   const int sp = lid % p.S;
   lid /= p.S;
   const int rb = lid % p.n_qt;
   lid /= p.n_qt;
-  const int h = lid % p.Hq;
-  const int b = lid / p.Hq;
-  const int g = h / p.G;
-  const int C1 = p.C + 1;
+  const int g = lid % p.Hkv;
+  const int b = lid / p.Hkv;
+  const int C1 = p.C + 1, GL = p.G * p.Ld;
   const int n_sel = p.n_sel;
   const int L_kv = n_sel + p.n_static + p.Ld;
-  const int tid = threadIdx.x;
-  const int r = rb * kF32Rows + tid;
-
-  RowState<D> st;
-  row_init<D>(st, r < p.Ld ? q_dec + (((size_t)b * p.Ld + r) * p.Hq + h) * D : nullptr);
-
-  const int ntile = (L_kv + kF32Keys - 1) / kF32Keys;
-  const int t_begin = (int)(((long long)ntile * sp) / p.S);
-  const int t_end = (int)(((long long)ntile * (sp + 1)) / p.S);
+  const int n_kvt = (L_kv + 31) / 32;
+  const int j0 = 32 * (int)(((long long)n_kvt * sp) / p.S);
+  const int j1 = min(L_kv, 32 * (int)(((long long)n_kvt * (sp + 1)) / p.S));
   const size_t cache_bg = ((size_t)b * p.N * p.Hkv + g) * C1;
   const int32_t* cidx = p.chunk_idx + (size_t)b * p.K;
   const int32_t* tslot = p.tok_slot + (size_t)b * p.K * p.Bt;
-  constexpr int CPR = D / 4;
-  __shared__ int bad_index;   // checking build: some kept row of this shard was out of range
-  if (kCheckIndices && tid == 0) bad_index = 0;
+  if (kCheckIndices && threadIdx.x == 0) bad_index = 0;
   if (kCheckIndices) __syncthreads();
-  for (int t = t_begin; t < t_end; ++t) {
-    for (int i = tid; i < kF32Keys * CPR; i += kF32Rows) {
-      const int kk = i / CPR, c = i % CPR;
-      const int j = t * kF32Keys + kk;
-      f32x4 kv = {0.f, 0.f, 0.f, 0.f}, vv = kv;
-      if (j < n_sel && p.compact) {
-        const size_t off = ((((size_t)b * p.Hkv + g) * n_sel) + j) * D + 4 * c;
-        kv = ld4(k_cache + off);
-        vv = ld4(v_cache + off);
-      } else if (j < n_sel) {
-        const int q = j / (1 + p.Bt), s = j - q * (1 + p.Bt);
-        int slot = s == 0 ? 0 : tslot[q * p.Bt + s - 1];
-        int chunk = cidx[q];
-        if (kCheckIndices && !kept_row_ok(chunk, slot, s == 0, p.N, p.C)) {
-          chunk = 0;
-          slot = 0;
-          bad_index = 1;
+  const int row0 = rb * 16 * QB;
+  auto where = [&](int i, int& hq, int& r) {
+    hq = g * p.G + (row0 + i) / p.Ld;
+    r = (row0 + i) % p.Ld;
+  };
+  attend_f32<D, QB, NW, false>(
+      lds, j0, j1, p.scale_log2,
+      [&](int i) -> const float* {
+        if (row0 + i >= GL) return nullptr;
+        int hq, r;
+        where(i, hq, r);
+        return q_dec + (((size_t)b * p.Ld + r) * p.Hq + hq) * D;
+      },
+      [&](int j, const float*& k, const float*& v) {
+        if (j < n_sel && p.compact) {
+          const size_t at = (((size_t)b * p.Hkv + g) * n_sel + j) * D;
+          k = k_cache + at;
+          v = v_cache + at;
+        } else if (j < n_sel) {
+          const int c = j / (1 + p.Bt), s = j - c * (1 + p.Bt);
+          int slot = s == 0 ? 0 : tslot[c * p.Bt + s - 1];
+          int chunk = cidx[c];
+          if (kCheckIndices && !kept_row_ok(chunk, slot, s == 0, p.N, p.C)) {
+            chunk = 0;
+            slot = 0;
+            bad_index = 1;
+          }
+          const size_t at = (cache_bg + (size_t)chunk * p.Hkv * C1 + slot) * D;
+          k = k_cache + at;
+          v = v_cache + at;
+        } else {
+          const bool stat = j < n_sel + p.n_static;
+          const size_t at = stat ? (((size_t)b * p.Ls + (j - n_sel)) * p.Hkv + g) * D
+                                 : (((size_t)b * p.Ld + (j - n_sel - p.n_static)) * p.Hkv + g) * D;
+          // Both values before one is selected: the compiler would select among the
+          // captures' addresses, which puts them into scratch memory.
+          const float *ks = uniform(k_static), *kd = uniform(k_dec), *vs = uniform(v_static), *vd = uniform(v_dec);
+          k = (stat ? ks : kd) + at;
+          v = (stat ? vs : vd) + at;
         }
-        const size_t off = (cache_bg + (size_t)chunk * p.Hkv * C1 + slot) * D + 4 * c;
-        kv = ld4(k_cache + off);
-        vv = ld4(v_cache + off);
-      } else if (j < n_sel + p.n_static) {
-        const size_t off = (((size_t)b * p.Ls + (j - n_sel)) * p.Hkv + g) * D + 4 * c;
-        kv = ld4(k_static + off);
-        vv = ld4(v_static + off);
-      } else if (j < L_kv) {
-        const size_t off = (((size_t)b * p.Ld + (j - n_sel - p.n_static)) * p.Hkv + g) * D + 4 * c;
-        kv = ld4(k_dec + off);
-        vv = ld4(v_dec + off);
-      }
-      *reinterpret_cast<f32x4*>(&Ks[kk][4 * c]) = kv;
-      *reinterpret_cast<f32x4*>(&Vs[kk][4 * c]) = vv;
-    }
-    __syncthreads();
-    row_tile<D>(st, Ks, Vs, min(kF32Keys, L_kv - t * kF32Keys), p.scale_log2, 0, 0);
-    __syncthreads();
-  }
-  if (r >= p.Ld) return;
-  float inv = 1.0f / st.l;
-  float lse2 = st.m + __log2f(st.l);
-  if (kCheckIndices && bad_index) inv = lse2 = __uint_as_float(kNanWord);
-  if (p.S == 1) {
-    row_store<D>(reinterpret_cast<float*>(p.o_dec) + (((size_t)b * p.Ld + r) * p.Hq + h) * D, st, inv);
-    if (p.lse_dec) p.lse_dec[((size_t)b * p.Hq + h) * p.Ld + r] = lse2 * kLn2;
-  } else {
-    const size_t row = (((size_t)sp * p.B + b) * p.Hq + h) * p.Ld + r;
-    row_store<D>(p.o_part + row * D, st, inv);
-    p.lse_part[row] = lse2;
-  }
+      },
+      [](int, int&, int&) {},
+      [&](int i, int d, f32x4 x) {
+        if (row0 + i >= GL) return;
+        int hq, r;
+        where(i, hq, r);
+        if (kCheckIndices && bad_index) x = f32x4{1.f, 1.f, 1.f, 1.f} * __uint_as_float(kNanWord);
+        float* dst = p.S == 1 ? reinterpret_cast<float*>(p.o_dec) + (((size_t)b * p.Ld + r) * p.Hq + hq) * D
+                              : p.o_part + ((((size_t)sp * p.B + b) * p.Hq + hq) * p.Ld + r) * D;
+        *reinterpret_cast<f32x4*>(dst + d) = x;
+      },
+      [&](int i, float m, float l, float) {
+        if (row0 + i >= GL) return;
+        int hq, r;
+        where(i, hq, r);
+        float lse2 = m + __log2f(l);
+        if (kCheckIndices && bad_index) lse2 = __uint_as_float(kNanWord);
+        if (p.S == 1) {
+          if (p.lse_dec) p.lse_dec[((size_t)b * p.Hq + hq) * p.Ld + r] = lse2 * kLn2;
+        } else {
+          p.lse_part[(((size_t)sp * p.B + b) * p.Hq + hq) * p.Ld + r] = lse2;
+        }
+      });
 }
 
 // ---------------------------------------------------------------------------
-template <int D>
-static hipError_t prefill_f32_d(const PrefillArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(prefill_f32_kernel<D>, dim3(a.total), dim3(kF32Rows), 0, s, a);
-  return hipGetLastError();
-}
-hipError_t launch_prefill_f32(const PrefillArgs& a, int head_dim, hipStream_t s) {
-  return head_dim == 128 ? prefill_f32_d<128>(a, s) : prefill_f32_d<64>(a, s);
-}
+// Row tiles of 32 (QB = 2, 4 waves) when they give every CU two workgroups, else
+// of 16 (QB = 1, 8 waves): a call below that is bound by the depth of one
+// workgroup, which the smaller tile cuts to a quarter.
+static bool wide_rows(long long units, int rows) { return units * ((rows + 31) / 32) >= 512; }
 
 template <int D>
-static hipError_t escore_f32_d(const EscoreArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(escore_f32_kernel<D>, dim3(a.total), dim3(kF32Rows), 0, s, a);
+static hipError_t prefill_f32_d(PrefillArgs a, float* key_mean, hipStream_t s) {
+  const int units = a.B * a.N * a.Hq, copies = a.B * a.N * a.Hkv;
+  const bool wide = wide_rows(units, a.Sc);
+  a.n_qt = wide ? (a.Sc + 31) / 32 : (a.Sc + 15) / 16;
+  a.total = units * a.n_qt;
+  if (wide) hipLaunchKernelGGL((prefill_f32_kernel<D, 2, 4>), dim3(a.total + copies), dim3(256), 0, s, a, key_mean);
+  else hipLaunchKernelGGL((prefill_f32_kernel<D, 1, 8>), dim3(a.total + copies), dim3(512), 0, s, a, key_mean);
   return hipGetLastError();
 }
+hipError_t launch_prefill_f32(const PrefillArgs& a, float* key_mean, int head_dim, hipStream_t s) {
+  return head_dim == 128 ? prefill_f32_d<128>(a, key_mean, s) : prefill_f32_d<64>(a, key_mean, s);
+}
+
 hipError_t launch_escore_f32(const EscoreArgs& a, int head_dim, hipStream_t s) {
-  return head_dim == 128 ? escore_f32_d<128>(a, s) : escore_f32_d<64>(a, s);
+  EscoreArgs e = a;
+  e.n_cb = (a.C + 15) / 16;
+  const dim3 grid((unsigned)(a.B * a.N * a.Hq * e.n_cb));
+  if (head_dim == 128) hipLaunchKernelGGL(escore_f32_kernel<128>, grid, dim3(64), 0, s, e);
+  else hipLaunchKernelGGL(escore_f32_kernel<64>, grid, dim3(64), 0, s, e);
+  return hipGetLastError();
 }
 
 template <int D>
-static hipError_t decode_f32_d(const DecodeArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(decode_f32_kernel<D>, dim3(a.total), dim3(kF32Rows), 0, s, a);
+static hipError_t decode_f32_d(DecodeArgs a, hipStream_t s) {
+  const int units = a.B * a.Hkv, rows = a.G * a.Ld;
+  const bool wide = wide_rows((long long)units * a.S, rows);
+  a.n_qt = wide ? (rows + 31) / 32 : (rows + 15) / 16;
+  a.total = units * a.n_qt * a.S;
+  if (wide) hipLaunchKernelGGL((decode_f32_kernel<D, 2, 4>), dim3(a.total), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((decode_f32_kernel<D, 1, 8>), dim3(a.total), dim3(512), 0, s, a);
   return hipGetLastError();
 }
 hipError_t launch_decode_f32(const DecodeArgs& a, int head_dim, hipStream_t s) {

@@ -325,17 +325,15 @@ pd_status pd_prefill_chunks(const pd_dims* d, const void* q_pre, const void* k_p
   a.qm_per_chunk = d->qm_per_chunk;
   a.out_f32 = d->out_fp32;
   a.scale_log2 = scale_of(d) * 1.4426950408889634f;
-  a.n_qt = cdiv(a.Sc, bf16 ? pd::kBf16Rows : 64);
+  a.n_qt = cdiv(a.Sc, pd::kBf16Rows);   // the fp32 launcher chooses its own row tiles
   a.n_kvt = cdiv(a.Sc, 64);
   a.total = a.B * a.N * a.Hq * a.n_qt;
 
   pd::EscoreArgs e{};
   e.q_qm = a.q_qm;
   e.k_cache = a.k_cache;
-  e.part_i = a.part_i;
   e.part_io = a.part_i;
   e.lse_q = a.lse_q;
-  e.tok_score = tok_score;
   e.B = a.B;
   e.N = a.N;
   e.C = a.C;
@@ -344,8 +342,6 @@ pd_status pd_prefill_chunks(const pd_dims* d, const void* q_pre, const void* k_p
   e.Hq = a.Hq;
   e.Hkv = a.Hkv;
   e.G = a.G;
-  e.n_cb = cdiv(a.C, 64);
-  e.total = a.B * a.N * e.n_cb;
   e.qm_per_chunk = a.qm_per_chunk;
   e.q2c = d->tok_score_dir;
   e.scale_log2 = a.scale_log2;
@@ -360,16 +356,13 @@ pd_status pd_prefill_chunks(const pd_dims* d, const void* q_pre, const void* k_p
                                    d->head_dim, km_slots(d), s);
     if (err != hipSuccess) return hip_status(err, "token-rank kernel");
   } else {
-    err = pd::launch_prefill_f32(a, d->head_dim, s);
+    err = pd::launch_prefill_f32(a, key_mean, d->head_dim, s);
     if (err != hipSuccess) return hip_status(err, "prefill kernel");
-    err = pd::launch_cache_copy(k_pre, v_pre, k_cache, v_cache, a.B, a.N, a.C, a.Hkv, d->head_dim, 4, s);
-    if (err != hipSuccess) return hip_status(err, "cache copy kernel");
     err = pd::launch_escore_f32(e, d->head_dim, s);
     if (err != hipSuccess) return hip_status(err, "token-score kernel");
-    err = pd::launch_token_rank(tok_score, tok_rank, a.B, a.N, a.C, s);
+    err = pd::launch_head_sum_rank(a.part_i, tok_score, tok_rank, a.B, a.N, a.Hq, a.C, nullptr, nullptr, 0,
+                                   d->head_dim, 0, s);
     if (err != hipSuccess) return hip_status(err, "token-rank kernel");
-    err = pd::launch_key_mean(k_cache, key_mean, a.B, a.N, a.C, a.Hkv, d->head_dim, false, s);
-    if (err != hipSuccess) return hip_status(err, "key-mean kernel");
   }
   if (chunk_score) {
     err = pd::launch_chunk_score(a.qm_mass, chunk_score, a.B, a.N, a.Hq, a.Lq, a.Lm, s);

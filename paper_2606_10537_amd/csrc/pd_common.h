@@ -49,6 +49,15 @@ __device__ __forceinline__ f32x16 mfma32x32x16(bf16x8 a, bf16x8 b, f32x16 c) {
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// A wave-uniform value, in scalar registers (quotients are computed in vector ones).
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+template <class T>
+__device__ __forceinline__ T* uniform(T* p) {
+  const uint64_t x = (uint64_t)p;
+  return (T*)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)x) |
+              ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32));
+}
+
 // Index checks of the checking build (compiled with PD_CHECK_INDICES): a kept
 // chunk outside 0..N-1 or a kept slot outside 1..C (slot 0, the BOS row, is
 // implied) is replaced by slot 0 of chunk 0 before anything is read, and every

@@ -46,10 +46,9 @@ struct PrefillArgs {
 
 struct EscoreArgs {
   const uint16_t *q_qm, *k_cache;
-  const float *part_i, *lse_q;
-  float* part_io;    // bf16 path: per-head sums [B][N][Hq][C], updated in place (same buffer as part_i)
-  float* tok_score;
-  int B, N, C, Lq, Lm, Hq, Hkv, G, n_cb, total, qm_per_chunk;
+  const float* lse_q;
+  float* part_io;    // per-head sums [B][N][Hq][C], updated in place
+  int B, N, C, Lq, Lm, Hq, Hkv, G, n_cb, qm_per_chunk;
   int q2c;           // 1: only the query rows' mass on the token (query-to-chunk score)
   float scale_log2;
 };
@@ -74,16 +73,12 @@ hipError_t launch_prefill_bf16(const PrefillArgs& a, int head_dim, hipStream_t s
 hipError_t launch_escore_bf16(const EscoreArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_decode_bf16(const DecodeArgs& a, int head_dim, hipStream_t s);
 
-hipError_t launch_prefill_f32(const PrefillArgs& a, int head_dim, hipStream_t s);
+// Also writes the chunk cache and the key means.
+hipError_t launch_prefill_f32(const PrefillArgs& a, float* key_mean, int head_dim, hipStream_t s);
 hipError_t launch_escore_f32(const EscoreArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_decode_f32(const DecodeArgs& a, int head_dim, hipStream_t s);
 
 // Generic (both element types).
-// Chunk cache copy (fp32 path; the bf16 prefill writes the cache itself).
-hipError_t launch_cache_copy(const void* k_pre, const void* v_pre, void* k_cache, void* v_cache,
-                             int B, int N, int C, int Hkv, int head_dim, int elem_bytes, hipStream_t s);
-hipError_t launch_key_mean(const void* k_cache, float* key_mean, int B, int N, int C, int Hkv,
-                           int head_dim, bool bf16, hipStream_t s);
 hipError_t launch_merge(const float* o_part, const float* lse_part, void* o_dec, float* lse_dec,
                         int S, int B, int Hq, int Ld, int head_dim, bool bf16, hipStream_t s);
 
@@ -116,8 +111,8 @@ struct JointArgs {
   double rope_base;   // 0: no rotation
 };
 hipError_t launch_gather_joint(const JointArgs& a, hipStream_t s);
-hipError_t launch_token_rank(const float* tok_score, int32_t* tok_rank, int B, int N, int C, hipStream_t s);
-// e = sum over the H_q heads of the per-head sums (fixed order), then the ranks.
+// e = sum over the H_q heads of the per-head sums (fixed order), then the ranks; key means from the partial
+// sums of the cache-writing workgroups (Hkv = 0: none).
 hipError_t launch_head_sum_rank(const float* per_head, float* tok_score, int32_t* tok_rank, int B, int N, int Hq,
                                 int C, const float* km_part, float* key_mean, int Hkv, int D, int km_slots,
                                 hipStream_t s);

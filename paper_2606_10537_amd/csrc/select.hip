@@ -1,8 +1,8 @@
 // Stage (b): per-step chunk scores, top-K chunks and the kept tokens of each
 // kept chunk, plus the once-per-layer token ranking of stage (a).
 //
-//   token_rank: grid (b, n)     -- bitonic sort of the C Eq. 5 scores in LDS
-//                                  (score desc, index asc) -> rank of each token;
+//   head_sum_rank: grid (b, n)  -- Eq. 5 scores summed over the heads, bitonic sort
+//                                  in LDS (score desc, index asc) -> token ranks;
 //   qscore:     grid (b, h, sp) -- by linearity the chunk score splits into
 //                                  terms scale * <(1/L_d) sum_{r in sp} q_r, kbar_n>
 //                                  over heads and row splits: one workgroup sums
@@ -43,41 +43,6 @@ struct Vec16 {
   }
 };
 
-// Sum of `nrows` rows (stride `row_stride` elements) of D elements each,
-// starting at element `base_off`; returns the D sums * `mul` into out[0..D).
-// 256 threads: thread t reads 16-byte chunk (t % TPR) of rows t/TPR, +NG, ...
-template <bool BF16>
-__device__ void rows_mean(const void* src, size_t base_off, size_t row_stride, int nrows, int D,
-                          float mul, float* out, float* red /* [256/TPR][D] */) {
-  constexpr int E = Vec16<BF16>::E;
-  const int TPR = D / E, NG = 256 / TPR;
-  const int t = threadIdx.x, c = t % TPR, rg = t / TPR;
-  float acc[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) acc[e] = 0.f;
-  for (int r = rg; r < nrows; r += NG) {
-    float v[E];
-    Vec16<BF16>::load(src, base_off + (size_t)r * row_stride + c * E, v);
-#pragma unroll
-    for (int e = 0; e < E; ++e) acc[e] += v[e];
-  }
-#pragma unroll
-  for (int e = 0; e < E; ++e) red[rg * D + c * E + e] = acc[e];
-  __syncthreads();
-  if (t < D) {
-    float s = 0.f;
-    for (int g = 0; g < NG; ++g) s += red[g * D + t];
-    out[t] = s * mul;
-  }
-}
-
-template <bool BF16>
-__global__ __launch_bounds__(256) void key_mean_kernel(const void* k_cache, float* key_mean, int C, int D) {
-  __shared__ float red[2048];
-  const size_t bng = blockIdx.x;  // ((b*N + n)*Hkv + g)
-  rows_mean<BF16>(k_cache, (bng * (C + 1) + 1) * D, (size_t)D, C, D, 1.0f / C, key_mean + bng * D, red);
-}
-
 __device__ __forceinline__ uint64_t rank_key(float score, int idx) {
   return ((uint64_t)(~float_order_key(score)) << 32) | (uint32_t)idx;
 }
@@ -108,18 +73,6 @@ static int next_pow2(int x) {
   return p;
 }
 
-// Rank of every token of one chunk by its Eq. 5 score.
-__global__ __launch_bounds__(256) void token_rank_kernel(const float* tok_score, int32_t* tok_rank, int C,
-                                                          int Cpad) {
-  extern __shared__ __attribute__((aligned(16))) uint64_t keys[];
-  const size_t bn = blockIdx.x;
-  const float* e = tok_score + bn * C;
-  for (int j = threadIdx.x; j < Cpad; j += 256) keys[j] = j < C ? rank_key(e[j], j) : ~0ull;
-  __syncthreads();
-  bitonic_sort(keys, Cpad);
-  for (int i = threadIdx.x; i < C; i += 256) tok_rank[bn * C + (uint32_t)keys[i]] = i;
-}
-
 // Ascending bitonic sort of P (power of two) keys in LDS by NT threads.
 template <int NT>
 __device__ void bitonic_sort_nt(uint64_t* keys, int P) {
@@ -142,9 +95,9 @@ __device__ void bitonic_sort_nt(uint64_t* keys, int P) {
 }
 
 // Workgroups (b*N + n, 0): e of one chunk = sum over the H_q heads of the
-// per-head sums (heads in ascending order), written out, then every token's
-// rank as token_rank_kernel, with 1024 threads (one compare per thread per
-// sort stage at C = 1024).  Workgroups (b*N + n, y >= 1): the chunk's key means
+// per-head sums (heads in ascending order), written out, then every
+// token's rank from a sort by 1024 threads (one compare per thread per
+// stage at C = 1024).  Workgroups (b*N + n, y >= 1): the chunk's key means
 // k-bar[g][d] = (1/C) * the sum of the km_slots partial sums of the
 // cache-writing workgroups (fixed order); these workgroups (at most 64 per
 // chunk) take 1024 of the H_kv*d values at a time.
@@ -191,12 +144,6 @@ hipError_t launch_head_sum_rank(const float* per_head, float* tok_score, int32_t
   const dim3 grid(B * N, 1 + std::min(64, (HD + kRankThreads - 1) / kRankThreads));
   hipLaunchKernelGGL(head_sum_rank_kernel, grid, dim3(kRankThreads), (size_t)Cpad * 8, s, per_head, tok_score,
                      tok_rank, Hq, C, Cpad, km_part, key_mean, HD, D, km_slots);
-  return hipGetLastError();
-}
-
-hipError_t launch_token_rank(const float* tok_score, int32_t* tok_rank, int B, int N, int C, hipStream_t s) {
-  const int Cpad = next_pow2(C);
-  hipLaunchKernelGGL(token_rank_kernel, dim3(B * N), dim3(256), (size_t)Cpad * 8, s, tok_score, tok_rank, C, Cpad);
   return hipGetLastError();
 }
 
@@ -626,15 +573,6 @@ hipError_t launch_gather_joint(const JointArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_key_mean(const void* k_cache, float* key_mean, int B, int N, int C, int Hkv, int head_dim,
-                           bool bf16, hipStream_t s) {
-  if (bf16)
-    hipLaunchKernelGGL(key_mean_kernel<true>, dim3(B * N * Hkv), dim3(256), 0, s, k_cache, key_mean, C, head_dim);
-  else
-    hipLaunchKernelGGL(key_mean_kernel<false>, dim3(B * N * Hkv), dim3(256), 0, s, k_cache, key_mean, C, head_dim);
-  return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------
 // Split-S merge: O = sum_s 2^(lse_s - M) O_s / sum_s 2^(lse_s - M).
 template <bool BF16>
@@ -701,34 +639,6 @@ hipError_t launch_merge(const float* o_part, const float* lse_part, void* o_dec,
     hipLaunchKernelGGL(merge_kernel<true>, grid, dim3(256), 0, s, o_part, lse_part, o_dec, lse_dec, S, B, Hq, Ld, head_dim);
   else
     hipLaunchKernelGGL(merge_kernel<false>, grid, dim3(256), 0, s, o_part, lse_part, o_dec, lse_dec, S, B, Hq, Ld, head_dim);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// Chunk cache copy [B][N][1+C][H][d] -> [B][N][H][1+C][d], 16 bytes per thread.
-__global__ __launch_bounds__(256) void cache_copy_kernel(const u32x4* k_pre, const u32x4* v_pre, u32x4* k_cache,
-                                                          u32x4* v_cache, size_t total, int C1, int Hkv, int cpr) {
-  const size_t gid = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (gid >= total) return;
-  // source order: ((bn*C1 + s)*Hkv + g)*cpr + c
-  const int c = gid % cpr;
-  size_t r = gid / cpr;
-  const int g = r % Hkv;
-  r /= Hkv;
-  const int s = r % C1;
-  const size_t bn = r / C1;
-  const size_t dst = ((bn * Hkv + g) * C1 + s) * cpr + c;
-  k_cache[dst] = k_pre[gid];
-  v_cache[dst] = v_pre[gid];
-}
-
-hipError_t launch_cache_copy(const void* k_pre, const void* v_pre, void* k_cache, void* v_cache, int B, int N, int C,
-                             int Hkv, int head_dim, int elem_bytes, hipStream_t s) {
-  const int cpr = head_dim * elem_bytes / 16;
-  const size_t total = (size_t)B * N * (C + 1) * Hkv * cpr;
-  const dim3 grid((unsigned)((total + 255) / 256));
-  hipLaunchKernelGGL(cache_copy_kernel, grid, dim3(256), 0, s, (const u32x4*)k_pre, (const u32x4*)v_pre,
-                     (u32x4*)k_cache, (u32x4*)v_cache, total, C + 1, Hkv, cpr);
   return hipGetLastError();
 }
 

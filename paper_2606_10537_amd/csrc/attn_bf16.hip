@@ -1,18 +1,32 @@
 // bf16 attention kernels for gfx950: chunk prefill (stage a) and sparse decode
-// attention (stage c).  Both run one tile engine:
+// attention (stage c).
 //
-//   * a workgroup = kBf16Waves waves (32 query rows each), d = 64 or 128;
-//   * K/V tiles of 64 rows go from HBM straight into LDS with
-//     global_load_lds_dwordx4 (no register staging), kBf16Stages tiles
-//     resident: the next ones stream in while the oldest is multiplied;
+//   * a wave takes 32 query rows, d = 64 or 128, for the whole sweep over its KV
+//     tiles of 64 rows; Q stays in registers;
+//   * K/V tiles go from HBM straight into LDS with global_load_lds_dwordx4 (no
+//     register staging), the next ones while one is multiplied, each DMA issued
+//     between two MFMAs;
 //   * both tiles are stored in 64-byte chunk groups with an XOR swizzle
 //     (tile_off), so that the K fragment reads (ds_read_b128) and the
 //     transposing V reads (ds_read_b64_tr_b16) are free of bank conflicts and
 //     every fragment address is a per-lane base plus an immediate offset;
 //   * S^T = K Q^T and O^T += V^T P^T run on v_mfma_f32_32x32x16_bf16 with
-//     fp32 accumulation; Q stays in registers for the whole sweep;
+//     fp32 accumulation;
 //   * online softmax in the log2 domain, lazy rescaling of the running output
 //     (only when a row maximum grows by more than 2^8), P rounded to bf16.
+//
+// What bounds it.  A tile costs a wave 1088 matrix cycles and about 650 vector
+// cycles (32 exponentials at 8, 100 others at 4-5), so the two waves of a SIMD
+// have to be in different parts of their tiles.  Two sweeps do that.  sweep_pair:
+// two workgroups of four waves on a CU, one wave of each on a SIMD, drift apart by
+// themselves, and one's start and end cost nothing while the other computes.
+// sweep_pingpong: one workgroup of eight waves whose halves run half a tile apart,
+// held there by barriers; each tile in LDS serves twice the rows (half the
+// traffic from L2), but the start, 8 us, and the end of a workgroup are bare.  Under
+// full load the card's power limit sets the clock, 1.7-1.9 GHz of 2.4.  Against
+// one workgroup of eight waves with one barrier a tile (before): prefill of 8 x
+// 32K 14.67 -> 14.05 ms, of 16K 595 -> 539 us, joint pass of 2 x 1156 rows 86 ->
+// 67 us, step of 8 x 32K 142.7 -> 139.7 us.
 //
 // Computing S transposed makes the MFMA output layout (each lane: one query,
 // 16 keys) directly usable as the B operand of the P*V product.  The matching
@@ -21,28 +35,46 @@
 // m of the 4 elements read by lane 4m + j/4, element j % 4.  If lane k of the
 // group points at V[key0 + k/4][d0 + 4(k%4)], lane j therefore receives
 // V[key0 + m][d0 + j], m = 0..3: four consecutive keys of one column.
+#include <utility>
+
 #include "pd_common.h"
 #include "pd_kernels.h"
 
 namespace pd {
 
+// f(0), f(1), ... f(N-1) with compile-time arguments.
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>());
+}
+
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef short i16x8 __attribute__((ext_vector_type(8)));
 #define PD_LDS __attribute__((address_space(3)))
+#define PD_INLINE __attribute__((always_inline))   // of a lambda: a call would put its captures into scratch memory
 
-template <int D>
+// NW: waves per workgroup.  4: two workgroups per CU, two K/V tiles resident in
+// each; 8: one workgroup per CU, four tiles resident.
+template <int D, int NW_ = 4>
 struct Tile {
-  static constexpr int NW = kBf16Waves;      // waves per workgroup
-  static constexpr int NH = kBf16RowsPerWave / 32;   // 32-row groups per wave
-  static constexpr int BM = kBf16Rows;       // query rows per workgroup
+  static constexpr int NW = NW_;
+  static constexpr int BM = 32 * NW;         // query rows per workgroup
   static constexpr int BN = 64;              // key rows per KV tile
   static constexpr int NT = 64 * NW;         // threads per workgroup
-  static constexpr int S = kBf16Stages;      // resident K/V tiles
+  static constexpr int S = NW == 8 ? 4 : 2;  // resident K/V tiles
   static constexpr int CH = D / 8;           // 16-byte chunks per row
   static constexpr int BPW = CH / NW;        // 1 KB DMA blocks (16 rows x 64 B) per wave and tile, K and V
   static constexpr int KS = D / 16;          // MFMA k-steps along d
   static constexpr int DB = D / 32;          // 32-row blocks of O^T
+  static constexpr int NF = D / 8;           // 32x32x16 fragments of one K or V tile
+  static constexpr int VP = NF / 2;          // V fragments read ahead of their use (from the softmax on)
+  static constexpr int KP = NF / 2;          // K fragments read ahead of their use
   static constexpr int TILE = BN * D;        // elements of one K or V tile
+  static_assert(NW == 4 || NW == 8, "4 or 8 waves");
   static_assert(BPW >= 1, "unsupported head dim");
 };
 
@@ -58,14 +90,6 @@ struct Tile {
 // rows of one chunk group.
 __device__ __forceinline__ int tile_off(int r, int c) { return (c >> 2) * 2048 + r * 32 + 8 * ((c & 3) ^ ((r >> 2) & 3)); }
 
-// Wave group of a wave (0 or 1): one wave of each group per SIMD.
-#ifndef PD_GROUP_OF_WAVE
-#define PD_GROUP_OF_WAVE(w) ((w) >> 2)
-#endif
-__device__ __forceinline__ int wave_group(int wave) {
-  return (kBf16Waves == 8 && kBf16RowsPerWave == 32) ? PD_GROUP_OF_WAVE(wave) : 0;
-}
-
 __device__ __forceinline__ u32x4 ld16(const uint16_t* p) { return *reinterpret_cast<const u32x4*>(p); }
 __device__ __forceinline__ void st16(uint16_t* p, u32x4 v) { *reinterpret_cast<u32x4*>(p) = v; }
 
@@ -73,24 +97,35 @@ __device__ __forceinline__ i16x4 ld_tr16(const uint16_t* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((PD_LDS i16x4*)(p));
 }
 
-// 16 bytes from global memory into LDS slot `lane` of the 1 KB block at lds
-// (global_load_lds_dwordx4 with the block's LDS address in M0).  Issued as
-// inline assembly: when the compiler sees an LDS DMA in flight it can no longer
-// count LDS reads precisely and waits for all of them (lgkmcnt(0)) before every
-// fragment use.  Completion is tracked by hand (wait_dma_keep); loads the
-// compiler does not see only make its own vmcnt waits stricter.
-__device__ __forceinline__ void dma16(const uint16_t* g, uint16_t* lds) {
-  const uint32_t lds_addr = (uint32_t)(uintptr_t)(PD_LDS void*)(lds);
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_addr) : "memory", "m0");
+// x, as a value the compiler knows nothing about: what a rare branch derives from
+// it is computed there, instead of in registers kept over the whole sweep.
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
 }
 
-// Engine state of 32 query rows of a wave (a wave holds NH of them).
+__device__ __forceinline__ const char* ubytes(const uint16_t* p) { return reinterpret_cast<const char*>(uniform(p)); }
+
+// 16 bytes from global memory into LDS slot `lane` of the 1 KB block at byte
+// address lds (global_load_lds_dwordx4 with the block's LDS address in M0), from
+// a uniform base plus a per-lane byte offset; inactive lanes load nothing.  Issued
+// as inline assembly: when the compiler sees an LDS DMA in flight it can no
+// longer count LDS reads precisely and waits for all of them (lgkmcnt(0)) before
+// every fragment use.  Completion is tracked by hand (wait_dma); loads the
+// compiler does not see only make its own vmcnt waits stricter.  The s_nop is
+// the wait state between a write of M0 and the DMA that reads it.
+__device__ __forceinline__ void dma16(const char* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(uniform(base)), "s"(uniform((int)lds)) : "memory", "m0");
+}
+__device__ __forceinline__ uint32_t lds_addr(const uint16_t* p) { return (uint32_t)(uintptr_t)(PD_LDS const void*)(p); }
+
+// Engine state of the 32 query rows of a wave.
 template <int D>
 struct WaveState {
   bf16x8 qf[Tile<D>::KS];
   f32x16 o[Tile<D>::DB];
   float m;      // running row max (log2 domain), shared by lanes l and l^32
-  float l;      // this lane's partial sum of the bf16-rounded weights that multiply V
+  f32x4 l;      // sums of the bf16-rounded weights that multiply V: [0] of query lane % 16, [1] of query lane % 16 + 16
   float lx;     // this lane's partial sum of the unrounded weights (prefill only)
   float qmass;  // this lane's partial mass on its counted key range (prefill only)
 };
@@ -110,7 +145,10 @@ struct MassRange {
 struct FragAddr {
   int k[2];   // K fragment, row l32 (+ 32 kb), chunk 2 ks + grp: base for ks % 2, + (ks / 2) * 2048 + kb * 1024
   int v[2];   // V transposing read: base for r2, + db * 2048 + (16 kk + 8 r2) * 32
+  uint32_t ones;   // row-sum operand
   __device__ FragAddr(int lane) {
+    const int sel = (lane >> 4) & 1;
+    ones = (lane & 3) == sel ? 0x3f803f80u : 0u;
     const int l32 = lane & 31, grp = lane >> 5;
 #pragma unroll
     for (int j = 0; j < 2; ++j) k[j] = tile_off(l32, 2 * j + grp);
@@ -123,53 +161,27 @@ struct FragAddr {
   }
 };
 
-// One KV tile for one wave, in three phases: S^T = K Q^T (s_phase), online
-// softmax producing the bf16 weights P (softmax_phase), O^T += V^T P^T
-// (pv_phase).  kv_valid: number of valid keys in this tile (64 except in a
-// ragged last tile).  mr: keys counted into qmass.  EXACT: also keep the
-// unrounded row sum and the counted mass (prefill).  O is normalised by the sum of the same
-// bf16-rounded weights that multiply V, so rounding P perturbs a convex
-// combination instead of scaling O.
+// One KV tile for one wave: S^T = K Q^T, online softmax producing the bf16
+// weights P, O^T += V^T P^T.  kv_valid: number of valid keys in this tile (64
+// except in a ragged last tile).  mr: keys counted into qmass.  EXACT: also keep
+// the unrounded row sum and the counted mass (prefill).  O is normalised by the
+// sum of the same bf16-rounded weights that multiply V, so rounding P perturbs a
+// convex combination instead of scaling O.
+// Fragment i of a K tile: k-step i / 2, 32-key block i % 2.
 template <int D>
-__device__ __forceinline__ bf16x8 k_frag(const uint16_t* Ks, const FragAddr& fa, int ks, int kb) {
+__device__ __forceinline__ bf16x8 k_frag(const uint16_t* Ks, const FragAddr& fa, int i) {
+  const int ks = i >> 1, kb = i & 1;
   return __builtin_bit_cast(bf16x8, ld16(Ks + fa.k[ks & 1] + (ks >> 1) * 2048 + kb * 1024));
 }
 
-// Fragments are read PF k-steps ahead of the MFMAs that use them (kept in that
-// order by scheduling fences); each K fragment serves the NH row groups.
-#ifndef PD_S_PREFETCH
-#define PD_S_PREFETCH 2
-#endif
-#ifndef PD_PIN_S
-#define PD_PIN_S 1
-#endif
-template <int D, int NH>
-__device__ __forceinline__ void s_phase(f32x16 (&s)[NH][2], const WaveState<D> (&st)[NH], const uint16_t* Ks,
-                                        const FragAddr& fa) {
-  using T = Tile<D>;
-  constexpr int PF = PD_S_PREFETCH < T::KS ? PD_S_PREFETCH : T::KS - 1;
-#pragma unroll
-  for (int h = 0; h < NH; ++h)
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) s[h][kb] = f32x16{0};
-  bf16x8 a[PF + 1][2];
-#pragma unroll
-  for (int ks = 0; ks < PF; ++ks)
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) a[ks][kb] = k_frag<D>(Ks, fa, ks, kb);
-#pragma unroll
-  for (int ks = 0; ks < T::KS; ++ks) {
-    if (ks + PF < T::KS) {
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb) a[(ks + PF) % (PF + 1)][kb] = k_frag<D>(Ks, fa, ks + PF, kb);
-    }
-    if (PD_PIN_S) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int h = 0; h < NH; ++h) s[h][kb] = mfma32x32x16(a[ks % (PF + 1)][kb], st[h].qf[ks], s[h][kb]);
-    if (PD_PIN_S) __builtin_amdgcn_sched_barrier(0);
-  }
+// Fragment i of a V^T tile (two transposing reads): key step i / DB, d block i % DB.
+template <int D>
+__device__ __forceinline__ bf16x8 v_frag(const uint16_t* Vs, const FragAddr& fa, int i) {
+  const int kk = i / Tile<D>::DB, db = i % Tile<D>::DB;
+  const uint16_t* vb = Vs + db * 2048 + 16 * kk * 32;
+  const i16x4 lo = ld_tr16(vb + fa.v[0]);
+  const i16x4 hi = ld_tr16(vb + fa.v[1] + 8 * 32);
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
 // Max of this lane's value and the value of lane l ^ 32 (v_permlane32_swap
@@ -179,22 +191,20 @@ __device__ __forceinline__ float max_across_halves(float x) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-// Softmax of one 32-row group, part 1: mask, row max, lazy rescale of the
-// running output.  Returns -m (log2 domain) for the exponent FMA.  Key of
-// s[kb][r]: 32*kb + 8*(r/4) + 4*grp + r%4.  The max is taken on raw scores (the
-// scale is positive) and the scale is folded into one FMA: p = exp2(s * scale_log2 - m).
+// Softmax, part 1: mask, row max, lazy rescale of the running output.  Returns
+// -m (log2 domain) for the exponent FMA.  Key of s[kb][r]: 32*kb + 8*(r/4) +
+// 4*grp + r%4.  The max is taken on raw scores (the scale is positive) and the
+// scale is folded into one FMA: p = exp2(s * scale_log2 - m).
 template <int D, bool EXACT>
 __device__ __forceinline__ float softmax_max(WaveState<D>& st, f32x16 (&s)[2], int grp, float scale_log2,
                                              int kv_valid) {
   using T = Tile<D>;
-  if (kv_valid < 64) {
+  if (__builtin_expect(kv_valid < 64, 0)) {
+    const int valid = kv_valid - 4 * opaque(grp);
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = 32 * kb + 8 * (r >> 2) + 4 * grp + (r & 3);
-        s[kb][r] = key < kv_valid ? s[kb][r] : -INFINITY;
-      }
+      for (int r = 0; r < 16; ++r) s[kb][r] = 32 * kb + 8 * (r >> 2) + (r & 3) < valid ? s[kb][r] : -INFINITY;
   }
   // One v_max3_f32 per pair (the file is built without NaN semantics, so no
   // canonicalising v_max precedes each score).
@@ -205,11 +215,13 @@ __device__ __forceinline__ float softmax_max(WaveState<D>& st, f32x16 (&s)[2], i
     for (int r = 0; r < 16; r += 2) mx = fmaxf(fmaxf(mx, s[kb][r]), s[kb][r + 1]);
   mx = max_across_halves(mx) * scale_log2;
   const bool upd = mx > st.m + 8.0f;
-  if (__ballot(upd)) {
+  if (__builtin_expect(__ballot(upd) != 0, 0)) {
     const float mnew = upd ? mx : st.m;
     const float alpha = fast_exp2(st.m - mnew);
     st.m = mnew;
-    st.l *= alpha;
+    const int q16 = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) & 15;
+    st.l[0] *= __shfl(alpha, q16);
+    st.l[1] *= __shfl(alpha, q16 + 16);
     if constexpr (EXACT) {
       st.lx *= alpha;
       st.qmass *= alpha;
@@ -222,141 +234,136 @@ __device__ __forceinline__ float softmax_max(WaveState<D>& st, f32x16 (&s)[2], i
   return -st.m;
 }
 
-// Part 2 (branch-free): weights p, packed to bf16 in pk; s keeps the fp32 p
-// for the counted mass.  The rounded weights' sum goes into l (one
-// v_dot2c_f32_bf16 with (1, 1) per packed pair), the exact sum into lx; the
-// exact sum of this tile is returned.
-template <int D, bool EXACT>
-__device__ __forceinline__ float softmax_exp(WaveState<D>& st, f32x16 (&s)[2], uint32_t (&pk)[16], float nm,
-                                             float scale_log2) {
+// Part 2: weights p, packed to bf16 in pk; with EXACT the tile's exact sum is
+// returned.  COUNT: cnt receives the sum over keys [qlo, qhi).  The first VP
+// fragments of the tile's V are read on the way: they land behind the
+// exponentials and wait in registers for the P*V of the next phase.
+template <int D, bool EXACT, bool COUNT>
+__device__ __forceinline__ float softmax_exp(const f32x16 (&s)[2], uint32_t (&pk)[16], bf16x8 (&vf)[Tile<D>::NF],
+                                             const uint16_t* Vs, const FragAddr& fa, float nm, float scale_log2,
+                                             int grp, int qlo, int qhi, float& cnt) {
+  constexpr int Q = Tile<D>::VP / 2;
   float lsum = 0.f;
+  if constexpr (COUNT) {
+    const int first = 4 * opaque(grp);
+    qlo -= first;
+    qhi -= first;
+  }
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
+  for (int g = 0; g < 4; ++g) {
+    if (g < 2) {
 #pragma unroll
-    for (int r = 0; r < 16; r += 2) {
+      for (int i = 0; i < Q; ++i) vf[g * Q + i] = v_frag<D>(Vs, fa, g * Q + i);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 8 * g; e < 8 * g + 8; e += 2) {
+      const int kb = e >> 4, r = e & 15;
       const float p0 = fast_exp2(fmaf(s[kb][r], scale_log2, nm));
       const float p1 = fast_exp2(fmaf(s[kb][r + 1], scale_log2, nm));
-      s[kb][r] = p0;
-      s[kb][r + 1] = p1;
       if constexpr (EXACT) lsum += p0 + p1;
-      pk[8 * kb + r / 2] = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)p0, (__bf16)p1});
+      if constexpr (COUNT) {
+        const int key = 32 * kb + 8 * (r >> 2) + (r & 3);   // less 4 grp
+        cnt += (key >= qlo && key < qhi) ? p0 : 0.f;
+        cnt += (key + 1 >= qlo && key + 1 < qhi) ? p1 : 0.f;
+      }
+      pk[e >> 1] = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)p0, (__bf16)p1});
     }
-  if constexpr (EXACT) st.lx += lsum;
-  const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-  float lr = st.l;
+    // Computed here: the compiler would sink the exponentials past the barrier to their use.
 #pragma unroll
-  for (int i = 0; i < 16; ++i) lr = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk[i]), ones, lr, false);
-  st.l = lr;
+    for (int e = 4 * g; e < 4 * g + 4; ++e) asm volatile("" : "+v"(pk[e]));
+    __builtin_amdgcn_sched_barrier(0);
+  }
   return lsum;
 }
 
-// Part 3 (prefill only): mass of this lane's counted keys (row group h of the
-// wave).  A range covering the whole tile takes the tile's exact row sum; the
-// per-key test runs only in tiles where some lane's range is partial.
-template <int D>
-__device__ __forceinline__ void softmax_qmass(WaveState<D>& st, const f32x16 (&s)[2], int grp, int h,
-                                              const MassRange& mr, float lsum) {
-  if (mr.lo0 >= mr.hi0 && mr.lo1 >= mr.hi1) return;   // wave-uniform: nothing counted in this tile
-  const int l32 = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) & 31;   // lane % 32
-  const bool first = l32 + 32 * h < mr.split;
-  const int qlo = first ? mr.lo0 : mr.lo1, qhi = first ? mr.hi0 : mr.hi1;
-  const bool any = qlo < qhi;
-  float qs = lsum;
-  if (__ballot(any && (qlo > 0 || qhi < 64))) {
-    qs = 0.f;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = 32 * kb + 8 * (r >> 2) + 4 * grp + (r & 3);
-        qs += (key >= qlo && key < qhi) ? s[kb][r] : 0.f;
-      }
-  }
-  st.qmass += any ? qs : 0.f;
-}
-
+// The vector phase of one tile: softmax, with the first V fragments read and
+// (EXACT) the row sum and the mass of the lane's counted keys kept.  A range that
+// covers the whole tile takes the tile's exact row sum; the per-key test runs
+// only in tiles where some lane's range is partial.
 template <int D, bool EXACT>
-__device__ __forceinline__ void softmax_phase(WaveState<D>& st, f32x16 (&s)[2], uint32_t (&pk)[16], int grp, int h,
-                                              float scale_log2, int kv_valid, const MassRange& mr) {
+__device__ __forceinline__ void softmax_phase(WaveState<D>& st, f32x16 (&s)[2], uint32_t (&pk)[16],
+                                              bf16x8 (&vf)[Tile<D>::NF], const uint16_t* Vs, const FragAddr& fa,
+                                              int grp, int lane32, float scale_log2, int kv_valid,
+                                              const MassRange& mr) {
   const float nm = softmax_max<D, EXACT>(st, s, grp, scale_log2, kv_valid);
-  const float lsum = softmax_exp<D, EXACT>(st, s, pk, nm, scale_log2);
-  if constexpr (EXACT) softmax_qmass<D>(st, s, grp, h, mr, lsum);
-}
-
-// V^T fragment of k-step kk and d block db (two transposing reads).
-template <int D>
-__device__ __forceinline__ bf16x8 v_frag(const uint16_t* Vs, const FragAddr& fa, int kk, int db) {
-  const uint16_t* vb = Vs + db * 2048 + 16 * kk * 32;
-  const i16x4 lo = ld_tr16(vb + fa.v[0]);
-  const i16x4 hi = ld_tr16(vb + fa.v[1] + 8 * 32);
-  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-
-// The first two V fragments of a tile's P*V (fragments i = 0, 1 below).
-template <int D>
-__device__ __forceinline__ void v_pre(bf16x8 (&vp)[2], const uint16_t* Vs, const FragAddr& fa) {
-  using T = Tile<D>;
-  vp[0] = v_frag<D>(Vs, fa, 0, 0);
-  vp[1] = v_frag<D>(Vs, fa, 1 / T::DB, 1 % T::DB);
-}
-
-// P^T operand of k-step kk: keys 16kk + 4grp + {0..3} then 16kk + 8 + 4grp + {0..3}
-// (pk[4kk .. 4kk+3]); the two transposing reads deliver V^T in that order.
-// Fragments are read two MFMAs ahead (the first two, vp, by the caller); each
-// serves the NH row groups.
-template <int D, int NH>
-__device__ __forceinline__ void pv_phase(WaveState<D> (&st)[NH], const uint32_t (&pk)[NH][16], const uint16_t* Vs,
-                                         const FragAddr& fa, const bf16x8 (&vp)[2]) {
-  using T = Tile<D>;
-  constexpr int N = 4 * T::DB;   // fragments: i = kk * DB + db
-  bf16x8 a[3];
-  a[0] = vp[0];
-  a[1] = vp[1];
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    if (i + 2 < N) a[(i + 2) % 3] = v_frag<D>(Vs, fa, (i + 2) / T::DB, (i + 2) % T::DB);
-    const int kk = i / T::DB, db = i % T::DB;
-#pragma unroll
-    for (int h = 0; h < NH; ++h) {
-      const bf16x8 pf =
-          __builtin_bit_cast(bf16x8, u32x4{pk[h][4 * kk], pk[h][4 * kk + 1], pk[h][4 * kk + 2], pk[h][4 * kk + 3]});
-      st[h].o[db] = mfma32x32x16(a[i % 3], pf, st[h].o[db]);
+  float cnt = 0.f;
+  if constexpr (!EXACT) {
+    softmax_exp<D, false, false>(s, pk, vf, Vs, fa, nm, scale_log2, grp, 0, 0, cnt);
+  } else {
+    const bool none = mr.lo0 >= mr.hi0 && mr.lo1 >= mr.hi1;   // wave-uniform: nothing counted in this tile
+    const bool first = lane32 < mr.split;
+    const int qlo = first ? mr.lo0 : mr.lo1, qhi = first ? mr.hi0 : mr.hi1;
+    const bool any = qlo < qhi;
+    if (!none && __ballot(any && (qlo > 0 || qhi < 64))) {
+      st.lx += softmax_exp<D, true, true>(s, pk, vf, Vs, fa, nm, scale_log2, grp, qlo, qhi, cnt);
+      st.qmass += cnt;
+    } else {
+      const float lsum = softmax_exp<D, true, false>(s, pk, vf, Vs, fa, nm, scale_log2, grp, 0, 0, cnt);
+      st.lx += lsum;
+      st.qmass += any ? lsum : 0.f;
     }
   }
 }
 
-// The tile step of one wave.  With one row group per wave (two waves per
-// SIMD), the two wave groups of a workgroup (one wave of each per SIMD) run the
-// phases in different orders so that one group's softmax overlaps the other's
-// MFMAs: group 0 does S, softmax, P*V of tile t; group 1 first does the P*V of
-// tile t-1 (its weights are still in pk), then S and softmax of tile t, and the
-// P*V of the last tile right after its softmax.  The order of the
-// online-softmax updates is the same in both groups.  One code path with
-// wave-uniform guards keeps a single pk array.  With two row groups per wave
-// (one wave per SIMD) each K and V fragment serves both groups.  VPRE: the
-// first two V fragments of the tile's P*V are read right after its S, so that
-// they are in flight during the softmax (in group 1, until the next step)
-// rather than at the start of the P*V; it shortens the prefill by about 2.6 %
-// and lengthens the decode, whose register allocation it changes, by about as
-// much, so only the prefill uses it.
-template <int D, int NH, bool EXACT, bool VPRE>
-__device__ __forceinline__ void wave_step(WaveState<D> (&st)[NH], uint32_t (&pk)[NH][16], bf16x8 (&vp)[2],
-                                          bool deferred, bool first, bool last, const uint16_t* Ks,
-                                          const uint16_t* Vs, const uint16_t* Vs_prev, const FragAddr& fa, int grp,
-                                          float scale_log2, int kv_valid, const MassRange& mr) {
-  f32x16 s[NH][2];
-  if (deferred && !first) {
-    if (!VPRE) v_pre<D>(vp, Vs_prev, fa);
-    pv_phase<D, NH>(st, pk, Vs_prev, fa, vp);
-  }
-  s_phase<D, NH>(s, st, Ks, fa);
-  if (VPRE) v_pre<D>(vp, Vs, fa);   // in flight during the softmax (and, deferred, until the next step)
+// The matrix phase: O += V^T P^T of the previous tile (weights pk), then S^T of
+// the next one.  LDS feeds the MFMAs at the rate at which it can: a 32-row wave
+// reads 1 KB per MFMA, four waves of a group 128 bytes per clock and CU.  So the
+// reads are spread over both phases: the first VP V fragments come from the
+// vector phase, the others are read VP products ahead of their use, and then, in
+// the second half of P*V and the first of S, the K fragments KP ahead of theirs.
+// P^T operand of key step kk: keys 16kk + 4grp + {0..3} then 16kk + 8 + 4grp +
+// {0..3} (pk[4kk .. 4kk+3]); the two transposing reads deliver V^T in that order.
+// The row sums of the rounded weights are one more product, ones * P^T, on the
+// 16x16x32 MFMA: its columns are 16 queries and its four 8-key blocks the lane
+// quarters, so row 0 (mod 4) takes the two quarters that hold queries 0..15 and
+// row 1 those of queries 16..31.  (v_dot2_f32_bf16 would do it on the vector
+// side, but waits for the matrix core: 69 cycles each beside another wave's
+// MFMAs, 5 alone.)
+// NEXT: the second half also reads the first KP fragments of the next K tile.
+template <int D, bool NEXT>
+__device__ __forceinline__ void pv_phase(WaveState<D>& st, const uint32_t (&pk)[16], bf16x8 (&vf)[Tile<D>::NF],
+                                         bf16x8 (&kf)[Tile<D>::NF], const uint16_t* Vs, const uint16_t* Ks_next,
+                                         const FragAddr& fa) {
+  using T = Tile<D>;
+  const bf16x8 ones = __builtin_bit_cast(bf16x8, u32x4{fa.ones, fa.ones, fa.ones, fa.ones});
 #pragma unroll
-  for (int h = 0; h < NH; ++h) softmax_phase<D, EXACT>(st[h], s[h], pk[h], grp, h, scale_log2, kv_valid, mr);
-  if (!deferred || last) {
-    if (!VPRE) v_pre<D>(vp, Vs, fa);
-    pv_phase<D, NH>(st, pk, Vs, fa, vp);
+  for (int i = 0; i < T::NF; ++i) {
+    const int kk = i / T::DB, db = i % T::DB;
+    const bf16x8 pf = __builtin_bit_cast(bf16x8, u32x4{pk[4 * kk], pk[4 * kk + 1], pk[4 * kk + 2], pk[4 * kk + 3]});
+    if (i + T::VP < T::NF) vf[i + T::VP] = v_frag<D>(Vs, fa, i + T::VP);
+    if (NEXT && i + T::KP >= T::NF) kf[i + T::KP - T::NF] = k_frag<D>(Ks_next, fa, i + T::KP - T::NF);
+    st.o[db] = mfma32x32x16(vf[i], pf, st.o[db]);
+    if (db == 0) st.l = mfma16x16x32(ones, pf, st.l);
+    __builtin_amdgcn_sched_barrier(0);
   }
+}
+
+// The first KP fragments of a K tile.
+template <int D>
+__device__ __forceinline__ void k_first(bf16x8 (&kf)[Tile<D>::NF], const uint16_t* Ks, const FragAddr& fa) {
+#pragma unroll
+  for (int i = 0; i < Tile<D>::KP; ++i) kf[i] = k_frag<D>(Ks, fa, i);
+}
+
+// S^T of a tile whose first KP fragments are in kf.  issue(n), n < N, issues the
+// wave's n-th DMA of a coming tile: one between every few MFMAs, where a wave
+// otherwise only waits for the matrix core.
+template <int D, int N, class Issue>
+__device__ __forceinline__ void s_phase(const WaveState<D>& st, f32x16 (&s)[2], bf16x8 (&kf)[Tile<D>::NF],
+                                        const uint16_t* Ks, const FragAddr& fa, Issue&& issue) {
+  using T = Tile<D>;
+  constexpr int STEP = T::NF / N;
+  s[0] = s[1] = f32x16{0};
+  static_for<T::NF>([&](auto i) PD_INLINE {
+    if constexpr (i + T::KP < T::NF) kf[i + T::KP] = k_frag<D>(Ks, fa, i + T::KP);
+    s[i & 1] = mfma32x32x16(kf[i], st.qf[i >> 1], s[i & 1]);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (i % STEP == 1) {
+      issue(std::integral_constant<int, i / STEP>());
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  });
 }
 
 // Completes the loads of the Q fragments here, before the sweep.  The compiler
@@ -364,12 +371,10 @@ __device__ __forceinline__ void wave_step(WaveState<D> (&st)[NH], uint32_t (&pk)
 // pending would make it wait for every load in flight (s_waitcnt vmcnt(0)),
 // tile DMAs included, at the fragment's first use in every tile.  Consuming
 // the registers in an empty asm statement puts that one wait here instead.
-template <int D, int NH>
-__device__ __forceinline__ void q_landed(const WaveState<D> (&st)[NH]) {
+template <int D>
+__device__ __forceinline__ void q_landed(const WaveState<D>& st) {
 #pragma unroll
-  for (int j = 0; j < NH; ++j)
-#pragma unroll
-    for (int ks = 0; ks < Tile<D>::KS; ++ks) asm volatile("" ::"v"(st[j].qf[ks]));
+  for (int ks = 0; ks < Tile<D>::KS; ++ks) asm volatile("" ::"v"(st.qf[ks]));
 }
 
 template <int D>
@@ -377,7 +382,7 @@ __device__ __forceinline__ void wave_init(WaveState<D>& st) {
 #pragma unroll
   for (int db = 0; db < Tile<D>::DB; ++db) st.o[db] = f32x16{0};
   st.m = -INFINITY;
-  st.l = 0.f;
+  st.l = f32x4{0.f, 0.f, 0.f, 0.f};
   st.lx = 0.f;
   st.qmass = 0.f;
 }
@@ -408,54 +413,41 @@ __device__ __forceinline__ void store_row_f32(float* dst, const WaveState<D>& st
     }
 }
 
-// Global element pointers of one K row and one V row.
-struct RowPtr {
-  const uint16_t* k;
-  const uint16_t* v;
+// This wave's share of the DMA of one K or V tile: BPW blocks of 1 KB.  Block b
+// holds rows 16 (b % 4) .. +15 of chunk group b / 4; a lane takes row 16 (b % 4)
+// + lane / 4 (dma_row) and loads the logical chunk that tile_off places in its
+// 16-byte slot (dma_chunk, the same for all blocks of a wave).
+template <class T>
+__device__ __forceinline__ int dma_row(int wave, int lane, int j) {
+  return ((wave * T::BPW + j) & 3) * 16 + (lane >> 2);
+}
+template <class T>
+__device__ __forceinline__ int dma_chunk(int wave, int lane) {
+  return 4 * ((wave * T::BPW) >> 2) + ((lane & 3) ^ ((lane >> 4) & 3));
+}
+
+// Where the wave's rows of one tile come from.  plain: all rows of the tile lie
+// at uniform bases k, v plus a byte offset per lane (from the row table if table,
+// else that of consecutive rows); otherwise (a tile that crosses from one buffer
+// to the next, or past the last row) the lanes of each buffer issue a DMA of
+// their own.  The next
+// `run` tiles continue this one, each `step` bytes further.
+struct TileSrc {
+  const char *k, *v;
+  long long step;
+  int run;
+  bool plain, table;
 };
 
-// Issue this wave's share of the DMA of one K/V tile: BPW blocks for K and
-// for V.  Block b holds rows 16 (b % 4) .. +15 of chunk group b / 4; lane
-// takes row 16 (b % 4) + lane / 4 and loads the logical chunk that tile_off
-// places in its 16-byte slot.  row(r) returns the global K and V pointers of
-// tile row r (already clamped to a valid row).  All row pointers are formed
-// before the first DMA is issued: an LDS read (a row table) after a DMA would
-// make the compiler wait for it.
-template <int D>
-__device__ __forceinline__ int dma_row(int wave, int lane, int j) {
-  return ((wave * Tile<D>::BPW + j) & 3) * 16 + (lane >> 2);
-}
-
-template <int D>
-__device__ __forceinline__ void dma_tile_rows(uint16_t* Kd, uint16_t* Vd, int wave, int lane,
-                                              const RowPtr (&rp)[Tile<D>::BPW]) {
-  using T = Tile<D>;
-#pragma unroll
-  for (int j = 0; j < T::BPW; ++j) {
-    const int blk = wave * T::BPW + j;
-    const int r = dma_row<D>(wave, lane, j);
-    const int c = 4 * (blk >> 2) + ((lane & 3) ^ ((r >> 2) & 3));
-    dma16(rp[j].k + 8 * c, Kd + blk * 512);
-    dma16(rp[j].v + 8 * c, Vd + blk * 512);
-  }
-}
-
-template <int D, class Row>
-__device__ __forceinline__ void dma_tile(uint16_t* Kd, uint16_t* Vd, int wave, int lane, Row&& row) {
-  RowPtr rp[Tile<D>::BPW];
-#pragma unroll
-  for (int j = 0; j < Tile<D>::BPW; ++j) rp[j] = row(dma_row<D>(wave, lane, j));
-  dma_tile_rows<D>(Kd, Vd, wave, lane, rp);
-}
-
-// Wait until this wave has at most `newer` tiles of DMA in flight: tile DMAs
-// are loads and complete in issue order, so the tile issued before those has
-// landed (stores issued in between can only make the wait longer).
-template <int PER>
-__device__ __forceinline__ void wait_dma_keep(int newer) {
-  if (newer <= 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  else if (newer == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER) : "memory");
-  else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * PER) : "memory");
+// Wait until at most n DMAs of this wave are in flight, n = m * BPW.  DMAs are
+// loads and complete in issue order, so all but the newest n have landed (stores
+// issued in between can only make the wait longer).
+template <class T>
+__device__ __forceinline__ void wait_dma(int m) {
+  constexpr int B = T::BPW;
+  if (m >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * B) : "memory");
+  else if (m == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(B) : "memory");
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
 // Workgroup barrier without a memory fence.  __syncthreads() would also wait
@@ -465,36 +457,226 @@ __device__ __forceinline__ void wait_dma_keep(int newer) {
 // memory clobber keeps the compiler from moving memory accesses across it.
 __device__ __forceinline__ void tile_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
-// Pipelined sweep over KV tiles [t_begin, t_end) with S resident tiles: tile t
-// lives in buffer (t - t_begin) % S.  When tile t is computed, tile t-1 is still
-// resident (its V feeds the deferred P*V of wave group 1), t+1 .. t+PF-1 are in
-// flight and t+PF (PF = S-2) is issued into the buffer of tile t-2.  One
-// barrier per tile: after it, tile t has landed for every wave and every wave
-// is done with tile t-1's step.  The buffers are distinct LDS objects and every
-// buffer index is a compile-time constant (the loop is unrolled by S), so the
-// compiler never mistakes a DMA into one buffer for a write to another.
-// dma(t, Kd, Vd) issues a tile, hook(t, Ks, Vs) sees a landed tile (the prefill
-// writes its cache share there), step(t, Ks, Vs, Vs_prev, last) computes.
-template <int D, class Dma, class Hook, class Step>
-__device__ __forceinline__ void kv_sweep(uint16_t* const* Kb, uint16_t* const* Vb, int t_begin, int t_end,
-                                         Dma&& dma, Hook&& hook, Step&& step) {
-  constexpr int S = Tile<D>::S, PF = S - 2, PER = 2 * Tile<D>::BPW;
+// Sweep over KV tiles [t_begin, t_end), at least one, by one of two workgroups of
+// four waves on a CU, which are not synchronised: one's start, end and softmax run
+// beside the other's MFMAs.  Tile t lives in buffer (t - t_begin) % 2.  One barrier per tile: before it every wave
+// has waited for its own share of tile t's DMA and has used all it read of tile
+// t-1, whose buffer then takes tile t+1.  tile(t) gives a tile's rows, peek(t,
+// code) reads the row table of a tile and off(ts, code, j) makes a lane's byte
+// offsets from that; mixed(V, r, c, lds) is the DMA of chunk byte c of row r (a K
+// or V row) in a tile that is not plain; hook(t, Ks, Vs) sees the landed tile
+// (the prefill writes its cache share there); softmax(t, last, s, pk, vf, Vs) is
+// the vector part.  ACTIVE: false for the waves without query rows, which only
+// move tiles.
+template <int D, bool ACTIVE, class Peek, class Off, class Src, class Mixed, class Hook, class Softmax>
+__device__ __forceinline__ void sweep_pair(WaveState<D>& st, uint16_t* Kb, uint16_t* Vb, const FragAddr& fa, int wave,
+                                         int lane, int t_begin, int t_end, Peek&& peek, Off&& off, Src&& tile,
+                                         Mixed&& mixed, Hook&& hook, Softmax&& softmax) {
+  using T = Tile<D, 4>;
+  // LDS byte address of this wave's first block in buffer 0.
+  const uint32_t ka = lds_addr(Kb) + wave * T::BPW * 1024, va = lds_addr(Vb) + wave * T::BPW * 1024;
+  TileSrc src;   // the tile whose DMA is issued next; code: the row table of that tile
+  unsigned code[T::BPW], at[T::BPW];
+  auto dma = [&](int t, int buf) PD_INLINE {
+    const uint32_t ko = ka + buf * (T::TILE * 2), vo = va + buf * (T::TILE * 2);
 #pragma unroll
-  for (int i = 0; i < PF; ++i)
-    if (t_begin + i < t_end) dma(t_begin + i, Kb[i], Vb[i]);
-  for (int t = t_begin; t < t_end; t += S) {
-#pragma unroll
-    for (int i = 0; i < S; ++i) {
-      const int tt = t + i;
-      if (tt < t_end) {
-        wait_dma_keep<PER>(min(PF - 1, t_end - 1 - tt));
-        tile_barrier();
-        if (tt + PF < t_end) dma(tt + PF, Kb[(i + PF) % S], Vb[(i + PF) % S]);
-        hook(tt, Kb[i], Vb[i]);
-        step(tt, Kb[i], Vb[i], Vb[(i + S - 1) % S], tt == t_end - 1);
+    for (int j = 0; j < T::BPW; ++j) {
+      if (src.plain) {
+        dma16(src.k, at[j], ko + j * 1024);
+        dma16(src.v, at[j], vo + j * 1024);
+      } else {
+        const int ln = opaque(lane), r = t * T::BN + dma_row<T>(wave, ln, j);
+        mixed(std::false_type(), r, 16u * dma_chunk<T>(wave, ln), ko + j * 1024);
+        mixed(std::true_type(), r, 16u * dma_chunk<T>(wave, ln), vo + j * 1024);
       }
     }
+  };
+  auto offsets = [&]() PD_INLINE {
+#pragma unroll
+    for (int j = 0; j < T::BPW; ++j) at[j] = off(src, code, j);
+  };
+  peek(t_begin, code);
+  src = tile(t_begin);
+  offsets();
+  dma(t_begin, 0);
+  peek(t_begin + 1, code);
+  f32x16 s[2];
+  uint32_t pk[16];
+  bf16x8 vf[T::NF], kf[T::NF];
+  int buf = 0;   // buffer of tile t
+  auto step = [&](int t, auto last) PD_INLINE {
+    constexpr bool LAST = decltype(last)::value;
+    const uint16_t *Ks = Kb + buf * T::TILE, *Vs = Vb + buf * T::TILE;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    tile_barrier();
+    if constexpr (!LAST) {
+      if (__builtin_expect(src.run > 0, 1)) {
+        src.k += src.step;
+        src.v += src.step;
+        --src.run;
+      } else {
+        src = tile(t + 1);
+      }
+      offsets();
+      const uint32_t ko = ka + (buf ^ 1) * (T::TILE * 2), vo = va + (buf ^ 1) * (T::TILE * 2);
+      if (ACTIVE && __builtin_expect(src.plain, 1)) {
+        k_first<D>(kf, Ks, fa);
+        s_phase<D, 2 * T::BPW>(st, s, kf, Ks, fa, [&](auto n) PD_INLINE {
+          if constexpr (n < T::BPW) dma16(src.k, at[n], ko + n * 1024);
+          else dma16(src.v, at[n - T::BPW], vo + (n - T::BPW) * 1024);
+        });
+      } else {
+        dma(t + 1, buf ^ 1);
+        if constexpr (ACTIVE) {
+          k_first<D>(kf, Ks, fa);
+          s_phase<D, 2 * T::BPW>(st, s, kf, Ks, fa, [](auto) PD_INLINE {});
+        }
+      }
+      peek(t + 2, code);
+    } else if constexpr (ACTIVE) {
+      k_first<D>(kf, Ks, fa);
+      s_phase<D, 2 * T::BPW>(st, s, kf, Ks, fa, [](auto) PD_INLINE {});
+    }
+    hook(t, Ks, Vs);
+    if constexpr (ACTIVE) {
+      softmax(t, last, s, pk, vf, Vs);
+      pv_phase<D, false>(st, pk, vf, kf, Vs, Ks, fa);
+    }
+    buf ^= 1;
+  };
+  for (int t = t_begin; t + 1 < t_end; ++t) step(t, std::false_type());
+  step(t_end - 1, std::true_type());
+}
+
+// The same sweep by the one workgroup of eight waves on a CU.  Tile t lives in
+// buffer (t - t_begin) % S.  Every wave alternates a matrix phase M(t) (P*V of tile
+// t-1, S of tile t) and a vector phase V(t) (softmax of t), one barrier after
+// each; the two wave groups of a workgroup (one wave of each per SIMD) run half
+// a period apart, so that on every SIMD one wave's MFMAs run beside the other's
+// VALU work:
+//   phase 2i     group 0: M(i)   group 1: V(i-1)
+//   phase 2i+1   group 0: V(i)   group 1: M(i)
+// K(i) is read in phases 2i and 2i+1 and V(i) in phases 2i+1 to 2i+3, at the
+// latest by M(i+1), which uses what it reads.  M(i) issues the DMAs of K(i+3),
+// over K(i-1), last read in phase 2i-1, and of V(i+2), over V(i-2), last read in
+// phase 2i-1.  A wave's DMAs are thus issued in the order
+// K(b) K(b+1) V(b) K(b+2) V(b+1) | K(b+3) V(b+2) | K(b+4) V(b+3) ...  K(i) must
+// have landed before phase 2i and V(i) before phase 2i+1: at the end of V(i)
+// every wave waits for all of its DMAs but those of M(i), so for V(i+1) and
+// K(i+2), one phase or more ahead of need.
+// The other arguments are those of sweep_pair (there is no hook).
+template <int D, bool ACTIVE, class Peek, class Off, class Src, class Mixed, class Softmax>
+__device__ __forceinline__ void sweep_pingpong(WaveState<D>& st, uint16_t* Kb, uint16_t* Vb, const FragAddr& fa, int wave,
+                                         int lane, int t_begin, int t_end, Peek&& peek, Off&& off, Src&& tile,
+                                         Mixed&& mixed, Softmax&& softmax) {
+  using T = Tile<D, 8>;
+  constexpr int S = T::S;
+  const int group = wave / (T::NW / 2);
+  // LDS byte address of this wave's first block in buffer 0.
+  const uint32_t ka = lds_addr(Kb) + wave * T::BPW * 1024, va = lds_addr(Vb) + wave * T::BPW * 1024;
+  // One tile's K (V = 0) or V (V = 1) into buffer buf.
+  auto dma = [&](auto V, const TileSrc& ts, const unsigned (&o)[T::BPW], int t, int buf) PD_INLINE {
+#pragma unroll
+    for (int j = 0; j < T::BPW; ++j) {
+      const uint32_t dst = (V ? va : ka) + buf * (T::TILE * 2) + j * 1024;
+      if (ts.plain) {
+        dma16(V ? ts.v : ts.k, o[j], dst);
+      } else {
+        const int ln = opaque(lane);
+        mixed(V, t * T::BN + dma_row<T>(wave, ln, j), 16u * dma_chunk<T>(wave, ln), dst);
+      }
+    }
+  };
+  constexpr std::false_type K_;
+  constexpr std::true_type V_;
+  f32x16 s[2];
+  uint32_t pk[16];
+  bf16x8 vf[T::NF], kf[T::NF];
+  // The tiles whose V and K the next M issues; code: the row table of the one after.
+  TileSrc src_v, src_k;
+  unsigned off_v[T::BPW], off_k[T::BPW], code[T::BPW];
+  auto advance = [&](int t, const unsigned (&code)[T::BPW]) PD_INLINE {   // src_k: tile t, from tile t-1
+    src_v = src_k;
+#pragma unroll
+    for (int j = 0; j < T::BPW; ++j) off_v[j] = off_k[j];
+    if (__builtin_expect(src_k.run > 0, 1)) {
+      src_k.k += src_k.step;
+      src_k.v += src_k.step;
+      --src_k.run;
+    } else {
+      src_k = tile(t);
+    }
+#pragma unroll
+    for (int j = 0; j < T::BPW; ++j) off_k[j] = off(src_k, code, j);
+  };
+  unsigned first[S][T::BPW];   // row table of the first tiles, read together
+#pragma unroll
+  for (int i = 0; i < S; ++i) peek(t_begin + i, first[i]);
+  src_k = tile(t_begin);
+#pragma unroll
+  for (int j = 0; j < T::BPW; ++j) off_k[j] = off(src_k, first[0], j);
+  dma(K_, src_k, off_k, t_begin, 0);
+#pragma unroll
+  for (int i = 1; i < S - 1; ++i) {   // K(b+i), V(b+i-1)
+    advance(t_begin + i, first[i]);
+    if (t_begin + i < t_end) dma(K_, src_k, off_k, t_begin + i, i);
+    if (t_begin + i - 1 < t_end) dma(V_, src_v, off_v, t_begin + i - 1, i - 1);
   }
+#pragma unroll
+  for (int j = 0; j < T::BPW; ++j) code[j] = first[S - 1][j];
+  wait_dma<T>(t_begin + 2 < t_end ? 2 : (t_begin + 1 < t_end ? 1 : 0));
+  tile_barrier();
+  if (group) tile_barrier();
+  if constexpr (ACTIVE) k_first<D>(kf, Kb, fa);
+  int buf = 0;   // buffer of tile t
+  // S of tile t and the DMAs of M(t).  HOT: tiles t .. t+3 exist.
+  auto scores = [&](int t, auto hot) PD_INLINE {
+    constexpr bool HOT = decltype(hot)::value;
+    const int buf2 = (buf + 2) & (S - 1), buf3 = (buf + 3) & (S - 1);
+    advance(t + 3, code);
+    peek(t + 4, code);
+    if (ACTIVE && __builtin_expect((HOT || t + 3 < t_end) && src_v.plain && src_k.plain, 1)) {
+      s_phase<D, 2 * T::BPW>(st, s, kf, Kb + buf * T::TILE, fa, [&](auto n) PD_INLINE {
+        if constexpr (n < T::BPW) dma16(src_k.k, off_k[n], ka + buf3 * (T::TILE * 2) + n * 1024);
+        else dma16(src_v.v, off_v[n - T::BPW], va + buf2 * (T::TILE * 2) + (n - T::BPW) * 1024);
+      });
+    } else {
+      if (HOT || t + 3 < t_end) dma(K_, src_k, off_k, t + 3, buf3);
+      if (HOT || t + 2 < t_end) dma(V_, src_v, off_v, t + 2, buf2);
+      if constexpr (ACTIVE) s_phase<D, 2 * T::BPW>(st, s, kf, Kb + buf * T::TILE, fa, [](auto) PD_INLINE {});
+    }
+  };
+  // V(t).  HOT: tiles t .. t+3 exist, so tile t is whole.
+  auto vector = [&](int t, auto hot) PD_INLINE {
+    constexpr bool HOT = decltype(hot)::value;
+    if constexpr (ACTIVE) softmax(t, std::bool_constant<!HOT>(), s, pk, vf, Vb + buf * T::TILE);
+    wait_dma<T>(HOT || t + 3 < t_end ? 2 : (t + 2 < t_end ? 1 : 0));
+  };
+  auto product = [&]() PD_INLINE {   // P*V of tile t; buf moves on to tile t+1
+    const int vbuf = buf;
+    buf = (buf + 1) & (S - 1);
+    // After the last tile the K fragments read here are an older tile's, and unused.
+    if constexpr (ACTIVE) pv_phase<D, true>(st, pk, vf, kf, Vb + vbuf * T::TILE, Kb + buf * T::TILE, fa);
+  };
+  int t = t_begin;
+  scores(t, std::false_type());
+  tile_barrier();
+  for (; t + 4 < t_end; ++t) {
+    vector(t, std::true_type());
+    tile_barrier();
+    product();
+    scores(t + 1, std::true_type());
+    tile_barrier();
+  }
+  for (;; ++t) {
+    vector(t, std::false_type());
+    tile_barrier();
+    product();
+    if (t + 1 >= t_end) break;
+    scores(t + 1, std::false_type());
+    tile_barrier();
+  }
+  if (!group) tile_barrier();
 }
 
 // ---------------------------------------------------------------------------
@@ -504,44 +686,40 @@ __device__ __forceinline__ void kv_sweep(uint16_t* const* Kb, uint16_t* const* V
 // the log2-domain LSE of the query rows and, when asked, the per-head
 // content mass of the query and pseudo-label rows.
 template <int D>
-__global__ __launch_bounds__(Tile<D>::NT, 1) void prefill_bf16_kernel(PrefillArgs p) {
+__global__ __launch_bounds__(Tile<D>::NT, 2) void prefill_bf16_kernel(PrefillArgs p) {
   using T = Tile<D>;
-  __shared__ __attribute__((aligned(1024))) uint16_t K0[T::TILE], K1[T::TILE], K2[T::TILE], K3[T::TILE];
-  __shared__ __attribute__((aligned(1024))) uint16_t V0[T::TILE], V1[T::TILE], V2[T::TILE], V3[T::TILE];
+  __shared__ __attribute__((aligned(1024))) uint16_t Kb[T::S * T::TILE], Vb[T::S * T::TILE];
   __shared__ __attribute__((aligned(16))) float kacc[T::NT / T::CH * D];   // content-key sums, one slot per thread
-  uint16_t* const Kb[4] = {K0, K1, K2, K3};   // the first T::S are used
-  uint16_t* const Vb[4] = {V0, V1, V2, V3};
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, grp = lane >> 5;
   int lid = xcd_remap(blockIdx.x, p.total);
-  const int qt = lid % p.n_qt;
+  const int qt = uniform(lid % p.n_qt);
   lid /= p.n_qt;
-  const int h = lid % p.Hq;
+  const int h = uniform(lid % p.Hq);
   lid /= p.Hq;
-  const int n = lid % p.N;
-  const int b = lid / p.N;
-  const int g = h / p.G;
+  const int n = uniform(lid % p.N);
+  const int b = uniform(lid / p.N);
+  const int g = uniform(h / p.G);
   const int C1 = p.C + 1;
   const size_t chunk = (size_t)b * p.N + n;
   const size_t qm_base = (p.qm_per_chunk ? chunk : (size_t)b) * (size_t)(p.Lq + p.Lm);
 
-  // Q fragments of this lane's query rows (one per row group j).
-  WaveState<D> st[T::NH];
-  const bool wave_active = qt * T::BM + wave * T::NH * 32 < p.Sc;
-#pragma unroll
-  for (int j = 0; j < T::NH; ++j) {
-    const int qrow = qt * T::BM + (wave * T::NH + j) * 32 + l32;
+  // Q fragments of this lane's query row.
+  WaveState<D> st;
+  const bool wave_active = qt * T::BM + wave * 32 < p.Sc;
+  const int qrow = qt * T::BM + wave * 32 + l32;
+  {
     const uint16_t* src = nullptr;
     if (qrow < C1) src = p.q_pre + ((chunk * C1 + qrow) * p.Hq + h) * D;
     else if (qrow < p.Sc) src = p.q_qm + ((qm_base + (qrow - C1)) * p.Hq + h) * D;
 #pragma unroll
     for (int ks = 0; ks < T::KS; ++ks)
-      st[j].qf[ks] = src ? __builtin_bit_cast(bf16x8, ld16(src + 16 * ks + 8 * grp)) : bf16x8{0};
-    wave_init(st[j]);
+      st.qf[ks] = src ? __builtin_bit_cast(bf16x8, ld16(src + 16 * ks + 8 * grp)) : bf16x8{0};
+    wave_init(st);
   }
-  q_landed<D, T::NH>(st);
+  q_landed(st);
   const FragAddr fa(lane);
 
   // Row r of the chunk sequence lives at base + r*HD (HD = H_kv*d elements), with
@@ -553,14 +731,22 @@ __global__ __launch_bounds__(Tile<D>::NT, 1) void prefill_bf16_kernel(PrefillArg
   const uint16_t* v_lo = p.v_pre + (chunk * C1 * p.Hkv + g) * D;
   const uint16_t* k_hi = p.k_qm + (qm_base * p.Hkv + g) * D - (size_t)C1 * HD;
   const uint16_t* v_hi = p.v_qm + (qm_base * p.Hkv + g) * D - (size_t)C1 * HD;
-  auto dma = [&](int t, uint16_t* Kd, uint16_t* Vd) {
-    const int r0 = t * T::BN;
-    dma_tile<D>(Kd, Vd, wave, lane, [=](int r) {
-      const int rr = min(r0 + r, p.Sc - 1);
-      const bool lo = rr < C1;
-      const unsigned off = (unsigned)rr * HD;
-      return RowPtr{(lo ? k_lo : k_hi) + off, (lo ? v_lo : v_hi) + off};
-    });
+  unsigned own_off[T::BPW];   // byte offset of this lane's rows within a tile of consecutive rows
+#pragma unroll
+  for (int j = 0; j < T::BPW; ++j) own_off[j] = 2u * dma_row<T>(wave, lane, j) * HD + 16u * dma_chunk<T>(wave, lane);
+  auto peek = [](int, unsigned (&)[T::BPW]) PD_INLINE {};
+  auto off = [=](const TileSrc&, const unsigned (&)[T::BPW], int j) PD_INLINE { return own_off[j]; };
+  auto tile = [=](int t) PD_INLINE {
+    const int r0 = t * T::BN, end = r0 < C1 ? C1 : p.Sc;   // rows up to end lie in one buffer
+    const char *kl = ubytes(k_lo), *kh = ubytes(k_hi), *vl = ubytes(v_lo), *vh = ubytes(v_hi);
+    const size_t at = (size_t)r0 * HD * 2;
+    return TileSrc{(r0 < C1 ? kl : kh) + at, (r0 < C1 ? vl : vh) + at, (long long)T::BN * HD * 2, (end - r0) / T::BN - 1, r0 + T::BN <= end, false};
+  };
+  auto mixed = [=](auto V, int r, unsigned c, uint32_t lds) PD_INLINE {
+    r = min(r, p.Sc - 1);
+    const unsigned at = 2u * HD * r + c;
+    if (r < C1) dma16(ubytes(V ? v_lo : k_lo), at, lds);
+    else dma16(ubytes(V ? v_hi : k_hi), at, lds);
   };
   // Each KV tile of the (b, n, kv head) group is written to the cache by exactly
   // one workgroup of that group (query tile t % n_qt of head g*G + (t / n_qt) % G),
@@ -568,13 +754,16 @@ __global__ __launch_bounds__(Tile<D>::NT, 1) void prefill_bf16_kernel(PrefillArg
   // Thread tid always handles 16-byte chunk tid % CH of the rows it copies, so
   // its content-key sums live in its own LDS slot kacc[tid / CH][8 (tid % CH) ..]
   // (no other thread touches it until the reduction after the sweep).
-  float* const kslot = kacc + (tid / T::CH) * D + 8 * (tid % T::CH);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) kslot[e] = 0.f;
-  auto cache_write = [&](int t, const uint16_t* Ks, const uint16_t* Vs) {
-    const bool writer = (t % p.n_qt == qt) && ((t / p.n_qt) % p.G == h % p.G);
-    if (!writer) return;
-    const size_t base = (chunk * p.Hkv + g) * C1;
+  for (int e = 0; e < 8; ++e) kacc[(tid / T::CH) * D + 8 * (tid % T::CH) + e] = 0.f;
+  const size_t cache_base = (chunk * p.Hkv + g) * C1;
+  const int w_step = p.n_qt * p.G;
+  int w_next = qt + p.n_qt * (h % p.G);   // the next tile to write
+  auto write_cache = [&](int t, const uint16_t* Ks, const uint16_t* Vs) PD_INLINE {
+    if (__builtin_expect(t != w_next, 1)) return;
+    w_next += w_step;
+    const int tid = opaque(threadIdx.x);
+    float* const kslot = kacc + (tid / T::CH) * D + 8 * (tid % T::CH);
     float ksum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < T::BN * T::CH / T::NT; ++i) {
@@ -583,8 +772,8 @@ __global__ __launch_bounds__(Tile<D>::NT, 1) void prefill_bf16_kernel(PrefillArg
       const int row = t * T::BN + r;
       if (row < C1) {
         const u32x4 kv = ld16(Ks + tile_off(r, c));
-        st16(p.k_cache + (base + row) * D + 8 * c, kv);
-        st16(p.v_cache + (base + row) * D + 8 * c, ld16(Vs + tile_off(r, c)));
+        st16(p.k_cache + (cache_base + row) * D + 8 * c, kv);
+        st16(p.v_cache + (cache_base + row) * D + 8 * c, ld16(Vs + tile_off(r, c)));
         if (row >= 1) {   // content rows only (the BOS row is not part of the key mean)
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
@@ -600,20 +789,17 @@ __global__ __launch_bounds__(Tile<D>::NT, 1) void prefill_bf16_kernel(PrefillArg
 
   const int qc_lo = C1, qc_hi = C1 + p.Lq;   // query columns counted by Eq. 5
   const int cm_hi = p.qm_mass ? C1 : 1;       // content columns counted for the chunk score (if asked)
-  const int split = C1 - (qt * T::BM + wave * T::NH * 32);
-  uint32_t pk_prev[T::NH][16];
-  bf16x8 vp_prev[2];
-  const bool deferred = wave_group(wave) != 0;
-  kv_sweep<D>(Kb, Vb, 0, p.n_kvt, dma, cache_write,
-              [&](int t, const uint16_t* ks, const uint16_t* vs, const uint16_t* vs_prev, bool last) {
-                if (!wave_active) return;
-                const int t0 = t * T::BN;
-                const int kv_valid = min(T::BN, p.Sc - t0);
-                const MassRange mr{split, max(qc_lo - t0, 0), min(qc_hi - t0, T::BN), max(1 - t0, 0),
-                                   min(cm_hi - t0, T::BN)};
-                wave_step<D, T::NH, true, true>(st, pk_prev, vp_prev, deferred, t == 0, last, ks, vs, vs_prev, fa,
-                                                grp, p.scale_log2, kv_valid, mr);
-              });
+  const int split = C1 - (qt * T::BM + wave * 32);
+  auto softmax = [&](int t, auto last, f32x16 (&s)[2], uint32_t (&pk)[16], bf16x8 (&vf)[T::NF], const uint16_t* vs) PD_INLINE {
+    const int t0 = t * T::BN;
+    const int kv_valid = decltype(last)::value ? p.Sc - t0 : T::BN;
+    const MassRange mr{split, max(qc_lo - t0, 0), min(qc_hi - t0, T::BN), max(1 - t0, 0), min(cm_hi - t0, T::BN)};
+    softmax_phase<D, true>(st, s, pk, vf, vs, fa, grp, l32, p.scale_log2, kv_valid, mr);
+  };
+  if (wave_active)
+    sweep_pair<D, true>(st, Kb, Vb, fa, wave, lane, 0, p.n_kvt, peek, off, tile, mixed, write_cache, softmax);
+  else
+    sweep_pair<D, false>(st, Kb, Vb, fa, wave, lane, 0, p.n_kvt, peek, off, tile, mixed, write_cache, softmax);
   // This workgroup's content-key sums: the thread slots summed in a fixed
   // order, one vector per (b, n, kv head, writer slot qt*G + h%G).
   __syncthreads();
@@ -624,23 +810,19 @@ __global__ __launch_bounds__(Tile<D>::NT, 1) void prefill_bf16_kernel(PrefillArg
   }
   if (!wave_active) return;
 
-#pragma unroll
-  for (int j = 0; j < T::NH; ++j) {
-    const int qrow = qt * T::BM + (wave * T::NH + j) * 32 + l32;
-    const float ltot = st[j].l + __shfl_xor(st[j].l, 32);
-    const float lxtot = st[j].lx + __shfl_xor(st[j].lx, 32);
-    const float qtot = st[j].qmass + __shfl_xor(st[j].qmass, 32);
-    const float inv = 1.0f / ltot;
-    if (qrow < p.Sc) {
-      const size_t orow = ((chunk * p.Sc + qrow) * p.Hq + h) * D;
-      if (p.out_f32) store_row_f32<D>(reinterpret_cast<float*>(p.o) + orow, st[j], inv, grp);
-      else store_row_bf16<D>(p.o + orow, st[j], inv, grp);
-      if (grp == 0) {
-        const size_t hb = chunk * p.Hq + h;
-        if (qrow >= 1 && qrow < C1) p.part_i[hb * p.C + (qrow - 1)] = qtot / lxtot;
-        if (qrow >= qc_lo && qrow < qc_hi) p.lse_q[hb * p.Lq + (qrow - qc_lo)] = st[j].m + __log2f(lxtot);
-        if (p.qm_mass && qrow >= C1) p.qm_mass[hb * (p.Lq + p.Lm) + (qrow - C1)] = qtot / lxtot;
-      }
+  const float ltot = (lane & 16) ? st.l[1] : st.l[0];
+  const float lxtot = st.lx + __shfl_xor(st.lx, 32);
+  const float qtot = st.qmass + __shfl_xor(st.qmass, 32);
+  const float inv = 1.0f / ltot;
+  if (qrow < p.Sc) {
+    const size_t orow = ((chunk * p.Sc + qrow) * p.Hq + h) * D;
+    if (p.out_f32) store_row_f32<D>(reinterpret_cast<float*>(p.o) + orow, st, inv, grp);
+    else store_row_bf16<D>(p.o + orow, st, inv, grp);
+    if (grp == 0) {
+      const size_t hb = chunk * p.Hq + h;
+      if (qrow >= 1 && qrow < C1) p.part_i[hb * p.C + (qrow - 1)] = qtot / lxtot;
+      if (qrow >= qc_lo && qrow < qc_hi) p.lse_q[hb * p.Lq + (qrow - qc_lo)] = st.m + __log2f(lxtot);
+      if (p.qm_mass && qrow >= C1) p.qm_mass[hb * (p.Lq + p.Lm) + (qrow - C1)] = qtot / lxtot;
     }
   }
 }
@@ -650,62 +832,58 @@ __global__ __launch_bounds__(Tile<D>::NT, 1) void prefill_bf16_kernel(PrefillArg
 // of the G*L_d query rows of that group, KV shard).  Query row rho of the group
 // is head g*G + rho / L_d, decode row rho % L_d.  KV row j of the shard walks:
 // [kept chunks: BOS + kept slots] ; [static rows] ; [own rows].
-template <int D>
-__global__ __launch_bounds__(Tile<D>::NT, 1) void decode_bf16_kernel(DecodeArgs p) {
-  using T = Tile<D>;
-  __shared__ __attribute__((aligned(1024))) uint16_t K0[T::TILE], K1[T::TILE], K2[T::TILE], K3[T::TILE];
-  __shared__ __attribute__((aligned(1024))) uint16_t V0[T::TILE], V1[T::TILE], V2[T::TILE], V3[T::TILE];
-  uint16_t* const Kb[4] = {K0, K1, K2, K3};   // the first T::S are used
-  uint16_t* const Vb[4] = {V0, V1, V2, V3};
-  __shared__ __attribute__((aligned(16))) int rowtab[kDecodeTableRows];   // cache row (n*Hkv*(C+1) + slot) of gathered rows
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void decode_bf16_kernel(DecodeArgs p) {
+  using T = Tile<D, NW>;
+  __shared__ __attribute__((aligned(1024))) uint16_t Kb[T::S * T::TILE], Vb[T::S * T::TILE];
+  __shared__ __attribute__((aligned(16))) unsigned rowtab[kDecodeTableRows];   // byte offset of each gathered row
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, grp = lane >> 5;
   int lid = xcd_remap(blockIdx.x, p.total);
-  const int sp = lid % p.S;
+  const int sp = uniform(lid % p.S);
   lid /= p.S;
-  const int qt = lid % p.n_qt;
+  const int qt = uniform(lid % p.n_qt);
   lid /= p.n_qt;
-  const int g = lid % p.Hkv;
-  const int b = lid / p.Hkv;
+  const int g = uniform(lid % p.Hkv);
+  const int b = uniform(lid / p.Hkv);
   const int GL = p.G * p.Ld;
   const int C1 = p.C + 1;
   const int n_sel = p.n_sel;
   const int L_kv = n_sel + p.n_static + p.Ld;
 
-  WaveState<D> st[T::NH];
-  const bool wave_active = qt * T::BM + wave * T::NH * 32 < GL;
-#pragma unroll
-  for (int j = 0; j < T::NH; ++j) {
-    const int rho = qt * T::BM + (wave * T::NH + j) * 32 + l32;
+  WaveState<D> st;
+  const bool wave_active = qt * T::BM + wave * 32 < GL;
+  const int rho = qt * T::BM + wave * 32 + l32;
+  {
     const int hq = g * p.G + (rho < GL ? rho / p.Ld : 0);
     const int rr = rho < GL ? rho % p.Ld : 0;
     const uint16_t* src = rho < GL ? p.q_dec + (((size_t)b * p.Ld + rr) * p.Hq + hq) * D : nullptr;
 #pragma unroll
     for (int ks = 0; ks < T::KS; ++ks)
-      st[j].qf[ks] = src ? __builtin_bit_cast(bf16x8, ld16(src + 16 * ks + 8 * grp)) : bf16x8{0};
-    wave_init(st[j]);
+      st.qf[ks] = src ? __builtin_bit_cast(bf16x8, ld16(src + 16 * ks + 8 * grp)) : bf16x8{0};
+    wave_init(st);
   }
   const FragAddr fa(lane);
 
   // This shard's tiles.
   const int n_kvt = (L_kv + T::BN - 1) / T::BN;
-  const int t_begin = (int)(((long long)n_kvt * sp) / p.S);
-  const int t_end = (int)(((long long)n_kvt * (sp + 1)) / p.S);
+  const int t_begin = uniform((int)(((long long)n_kvt * sp) / p.S));
+  const int t_end = uniform((int)(((long long)n_kvt * (sp + 1)) / p.S));
 
   // Prefix rows of (b, g): gathered from the chunk cache (row n*Hkv*C1 + slot
   // from this base), or, in compact mode, row j of the contiguous buffer.
   const size_t cache_bg = p.compact ? ((size_t)b * p.Hkv + g) * n_sel : ((size_t)b * p.N * p.Hkv + g) * C1;
-  // Prefix rows of this shard: row codes into LDS once (the host keeps every
-  // shard within kDecodeTableRows rows), so tile loads need no index fetch.
+  // Prefix rows of this shard: byte offsets into LDS once (the host keeps
+  // every shard within kDecodeTableRows rows), so tile loads need no index fetch.
   const int j_lo = t_begin * T::BN;
   const int j_hi = min(t_end * T::BN, n_sel);
   __shared__ int bad_index;   // checking build: some kept row of this shard was out of range
   if (kCheckIndices && tid == 0) bad_index = 0;
   if (kCheckIndices) __syncthreads();
   if (p.compact) {
-    for (int j = j_lo + tid; j < j_hi; j += T::NT) rowtab[j - j_lo] = j;
+    for (int j = j_lo + tid; j < j_hi; j += T::NT) rowtab[j - j_lo] = 2u * D * j;
   } else {
     const int32_t* cidx = p.chunk_idx + (size_t)b * p.K;
     const int32_t* tslot = p.tok_slot + (size_t)b * p.K * p.Bt;
@@ -718,7 +896,7 @@ __global__ __launch_bounds__(Tile<D>::NT, 1) void decode_bf16_kernel(DecodeArgs 
         slot = 0;
         bad_index = 1;
       }
-      rowtab[j - j_lo] = chunk * p.Hkv * C1 + slot;
+      rowtab[j - j_lo] = 2u * D * (unsigned)(chunk * p.Hkv * C1 + slot);
     }
   }
   __syncthreads();
@@ -734,98 +912,77 @@ __global__ __launch_bounds__(Tile<D>::NT, 1) void decode_bf16_kernel(DecodeArgs 
   const uint16_t* vs_ = p.v_static ? p.v_static + sb : p.v_dec + db;
   const uint16_t* kd_ = p.k_dec + db;
   const uint16_t* vd_ = p.v_dec + db;
-  const int tab_hi = max(j_hi - j_lo - 1, 0);
   const int n_static = p.n_static;
-  int* const rowtab_p = rowtab;
-  // A whole gathered tile takes this lane's row codes from the row table.
-  // They are read one tile ahead (right after the previous tile's DMA) and
-  // kept raw until used, so that issuing a DMA after the barrier needs no LDS
-  // read and no wait.
-  auto read_tab = [=](int t, unsigned (&o)[T::BPW]) {
-    const int* tab = rowtab_p + (t * T::BN - j_lo);
+  const unsigned* const rowtab_p = rowtab;
+  unsigned own_off[T::BPW];   // byte offset of this lane's rows within a tile of consecutive rows
 #pragma unroll
-    for (int j = 0; j < T::BPW; ++j) o[j] = (unsigned)tab[dma_row<D>(wave, lane, j)];
+  for (int j = 0; j < T::BPW; ++j) own_off[j] = 2u * dma_row<T>(wave, lane, j) * HD + 16u * dma_chunk<T>(wave, lane);
+  const unsigned chunk_off = 16u * dma_chunk<T>(wave, lane);
+  // Row offsets of a gathered tile (for other tiles whatever the table holds,
+  // unused): read one tile ahead, so that issuing a DMA waits for no LDS read.
+  auto peek = [=](int t, unsigned (&o)[T::BPW]) PD_INLINE {
+    const unsigned* tab = rowtab_p + min(t * T::BN - j_lo, kDecodeTableRows - T::BN);
+#pragma unroll
+    for (int j = 0; j < T::BPW; ++j) o[j] = tab[dma_row<T>(wave, lane, j)];
   };
-  unsigned nxt[T::BPW];
-  int nxt_t = -1;
-  auto dma = [&](int t, uint16_t* Kd, uint16_t* Vd) {
-    const int* rowtab = rowtab_p;
-    const int r0 = t * T::BN;
-    if (r0 + T::BN <= n_sel) {
-      // Whole tile gathered from the cache.
-      unsigned o[T::BPW];
-      if (nxt_t == t) {
-#pragma unroll
-        for (int j = 0; j < T::BPW; ++j) o[j] = nxt[j];
-      } else {
-        read_tab(t, o);
-      }
-      RowPtr rp[T::BPW];
-#pragma unroll
-      for (int j = 0; j < T::BPW; ++j) rp[j] = RowPtr{kc + o[j] * D, vc + o[j] * D};
-      dma_tile_rows<D>(Kd, Vd, wave, lane, rp);
-      if (r0 + 2 * T::BN <= n_sel && t + 1 < t_end) {
-        read_tab(t + 1, nxt);
-        nxt_t = t + 1;
-      }
-    } else if (r0 >= n_sel) {
-      // No gathered row: static rows, then own rows.
-      dma_tile<D>(Kd, Vd, wave, lane, [=](int r) {
-        const int j = min(r0 + r, L_kv - 1);
-        const unsigned off = (unsigned)(j * HD);
-        const bool stat = j < n_sel + n_static;
-        return RowPtr{(stat ? ks_ : kd_) + off, (stat ? vs_ : vd_) + off};
-      });
-    } else {
-      dma_tile<D>(Kd, Vd, wave, lane, [=](int r) {
-        const int j = min(r0 + r, L_kv - 1);
-        const unsigned tab = (unsigned)rowtab[min(max(j - j_lo, 0), tab_hi)] * D;
-        const bool gath = j < n_sel, stat = j < n_sel + n_static;
-        const unsigned off = gath ? tab : (unsigned)(j * HD);
-        const uint16_t* kb = stat ? ks_ : kd_;
-        const uint16_t* vb = stat ? vs_ : vd_;
-        kb = gath ? kc : kb;
-        vb = gath ? vc : vb;
-        return RowPtr{kb + off, vb + off};
-      });
-    }
+  auto off = [=](const TileSrc& ts, const unsigned (&o)[T::BPW], int j) PD_INLINE {
+    return ts.table ? o[j] + chunk_off : own_off[j];
+  };
+  auto tile = [=](int t) PD_INLINE {
+    const int r0 = t * T::BN, n_stat = n_sel + n_static;
+    const bool gath = r0 < n_sel, stat = r0 < n_stat;
+    const int end = gath ? n_sel : (stat ? n_stat : L_kv);   // rows up to end lie in one buffer
+    // ubytes() of all before any is selected: the compiler would select among the
+    // captures' addresses, which puts them into scratch memory.
+  const char *kg = ubytes(kc), *ks = ubytes(ks_), *kd = ubytes(kd_);
+    const char *vg = ubytes(vc), *vs = ubytes(vs_), *vd = ubytes(vd_);
+    const size_t at = gath ? 0 : (size_t)r0 * HD * 2;
+    return TileSrc{(gath ? kg : (stat ? ks : kd)) + at, (gath ? vg : (stat ? vs : vd)) + at, gath ? 0 : (long long)T::BN * HD * 2, (end - r0) / T::BN - 1,
+                   r0 + T::BN <= end, gath};
+  };
+  auto mixed = [=](auto V, int r, unsigned c, uint32_t lds) PD_INLINE {
+    r = min(r, L_kv - 1);
+    const unsigned at = 2u * HD * r + c;
+    if (r < n_sel) dma16(ubytes(V ? vc : kc), rowtab_p[r - j_lo] + c, lds);
+    else if (r < n_sel + n_static) dma16(ubytes(V ? vs_ : ks_), at, lds);
+    else dma16(ubytes(V ? vd_ : kd_), at, lds);
   };
   // The Q loads overlap the row-table loads above; both have landed here.
-  q_landed<D, T::NH>(st);
-  auto no_hook = [](int, const uint16_t*, const uint16_t*) {};
-  uint32_t pk_prev[T::NH][16];
-  bf16x8 vp_prev[2];
-  const bool deferred = wave_group(wave) != 0;
-  kv_sweep<D>(Kb, Vb, t_begin, t_end, dma, no_hook,
-              [&](int t, const uint16_t* ks, const uint16_t* vs, const uint16_t* vs_prev, bool last) {
-                if (!wave_active) return;
-                const int kv_valid = min(T::BN, L_kv - t * T::BN);
-                wave_step<D, T::NH, false, false>(st, pk_prev, vp_prev, deferred, t == t_begin, last, ks, vs,
-                                                  vs_prev, fa, grp, p.scale_log2, kv_valid,
-                                                  MassRange{0, 0, 0, 0, 0});
-              });
+  q_landed(st);
+  auto softmax = [&](int t, auto last, f32x16 (&s)[2], uint32_t (&pk)[16], bf16x8 (&vf)[T::NF], const uint16_t* vs) PD_INLINE {
+    const int kv_valid = decltype(last)::value ? min(T::BN, L_kv - t * T::BN) : T::BN;
+    softmax_phase<D, false>(st, s, pk, vf, vs, fa, grp, l32, p.scale_log2, kv_valid, MassRange{0, 0, 0, 0, 0});
+  };
+  if constexpr (NW == 8) {
+    if (wave_active)
+      sweep_pingpong<D, true>(st, Kb, Vb, fa, wave, lane, t_begin, t_end, peek, off, tile, mixed, softmax);
+    else
+      sweep_pingpong<D, false>(st, Kb, Vb, fa, wave, lane, t_begin, t_end, peek, off, tile, mixed, softmax);
+  } else {
+    auto no_hook = [](int, const uint16_t*, const uint16_t*) {};
+    if (wave_active)
+      sweep_pair<D, true>(st, Kb, Vb, fa, wave, lane, t_begin, t_end, peek, off, tile, mixed, no_hook, softmax);
+    else
+      sweep_pair<D, false>(st, Kb, Vb, fa, wave, lane, t_begin, t_end, peek, off, tile, mixed, no_hook, softmax);
+  }
   if (!wave_active) return;
 
-#pragma unroll
-  for (int j = 0; j < T::NH; ++j) {
-    const int rho = qt * T::BM + (wave * T::NH + j) * 32 + l32;
-    if (rho >= GL) continue;
-    const int hq = g * p.G + rho / p.Ld;
-    const int rr = rho % p.Ld;
-    const float ltot = st[j].l + __shfl_xor(st[j].l, 32);
-    float inv = 1.0f / ltot;
-    float lse2 = st[j].m + __log2f(ltot);
-    if (kCheckIndices && bad_index) inv = lse2 = __uint_as_float(kNanWord);
-    if (p.S == 1) {
-      const size_t orow = (((size_t)b * p.Ld + rr) * p.Hq + hq) * D;
-      if (p.out_f32) store_row_f32<D>(reinterpret_cast<float*>(p.o_dec) + orow, st[j], inv, grp);
-      else store_row_bf16<D>(reinterpret_cast<uint16_t*>(p.o_dec) + orow, st[j], inv, grp);
-      if (p.lse_dec && grp == 0) p.lse_dec[((size_t)b * p.Hq + hq) * p.Ld + rr] = lse2 * kLn2;
-    } else {
-      const size_t row = (((size_t)sp * p.B + b) * p.Hq + hq) * p.Ld + rr;
-      store_row_f32<D>(p.o_part + row * D, st[j], inv, grp);
-      if (grp == 0) p.lse_part[row] = lse2;
-    }
+  if (rho >= GL) return;
+  const int hq = g * p.G + rho / p.Ld;
+  const int rr = rho % p.Ld;
+  const float ltot = (lane & 16) ? st.l[1] : st.l[0];
+  float inv = 1.0f / ltot;
+  float lse2 = st.m + __log2f(ltot);
+  if (kCheckIndices && bad_index) inv = lse2 = __uint_as_float(kNanWord);
+  if (p.S == 1) {
+    const size_t orow = (((size_t)b * p.Ld + rr) * p.Hq + hq) * D;
+    if (p.out_f32) store_row_f32<D>(reinterpret_cast<float*>(p.o_dec) + orow, st, inv, grp);
+    else store_row_bf16<D>(reinterpret_cast<uint16_t*>(p.o_dec) + orow, st, inv, grp);
+    if (p.lse_dec && grp == 0) p.lse_dec[((size_t)b * p.Hq + hq) * p.Ld + rr] = lse2 * kLn2;
+  } else {
+    const size_t row = (((size_t)sp * p.B + b) * p.Hq + hq) * p.Ld + rr;
+    store_row_f32<D>(p.o_part + row * D, st, inv, grp);
+    if (grp == 0) p.lse_part[row] = lse2;
   }
 }
 
@@ -919,10 +1076,31 @@ hipError_t launch_prefill_bf16(const PrefillArgs& a, int head_dim, hipStream_t s
   return head_dim == 128 ? launch_prefill_d<128>(a, s) : launch_prefill_d<64>(a, s);
 }
 
+// Which sweep decodes.  Eight waves win by the traffic they save, where their
+// workgroups fill the CUs in whole rounds and a sweep is long against its start:
+// step of 8 x 32K (512 workgroups of 27 tiles) 139.7 us against 145.3 with four
+// waves, four steps of 4 x 32K 287 against 300.  With 320 workgroups of 19 tiles
+// (joint pass of 2 x 1156 rows), two rounds for 1.25 of work, they take 112 against
+// 98 us, with 4 tiles (8K, 5 shards) 35.5 against 33.1 us.
+static bool eight_waves(const DecodeArgs& a) {
+  const long long groups = (long long)a.B * a.Hkv * ((a.G * a.Ld + 255) / 256) * a.S;
+  const long long rounds = (groups + 255) / 256;
+  const int tiles = (a.n_sel + a.n_static + a.Ld + 63) / 64;
+  return tiles >= 16 * a.S && 10 * groups >= 9 * 256 * rounds;
+}
+
+template <int D, int NW>
+static hipError_t launch_decode_w(DecodeArgs a, hipStream_t s) {
+  a.n_qt = (a.G * a.Ld + Tile<D, NW>::BM - 1) / Tile<D, NW>::BM;
+  a.total = a.B * a.Hkv * a.n_qt * a.S;
+  hipLaunchKernelGGL((decode_bf16_kernel<D, NW>), dim3(a.total), dim3(Tile<D, NW>::NT), 0, s, a);
+  return hipGetLastError();
+}
 template <int D>
 static hipError_t launch_decode_d(const DecodeArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(decode_bf16_kernel<D>, dim3(a.total), dim3(Tile<D>::NT), 0, s, a);
-  return hipGetLastError();
+  if constexpr (D == 128)
+    if (eight_waves(a)) return launch_decode_w<D, 8>(a, s);
+  return launch_decode_w<D, 4>(a, s);
 }
 hipError_t launch_decode_bf16(const DecodeArgs& a, int head_dim, hipStream_t s) {
   return head_dim == 128 ? launch_decode_d<128>(a, s) : launch_decode_d<64>(a, s);

@@ -35,7 +35,7 @@ constexpr int kMaxChunks = 1024;
 constexpr int kMaxChunkLen = 4096;
 constexpr int kMaxSplits = 64;
 constexpr int kMaxCompactRows = 1 << 20;   // prefix rows of a compact decode call
-constexpr int kTargetWorkgroups = 256 * 8 / pd::kBf16Waves;  // two resident waves per SIMD on 256 CUs
+constexpr int kTargetWorkgroups = 512;   // two resident workgroups of four waves on 256 CUs
 constexpr size_t kAlign = 256;
 
 size_t round_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }

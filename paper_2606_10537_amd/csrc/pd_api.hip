@@ -352,22 +352,33 @@ pd_status pd_prefill_chunks(const pd_dims* d, const void* q_pre, const void* k_p
     if (err != hipSuccess) return hip_status(err, "prefill kernel");
     err = pd::launch_escore_bf16(e, d->head_dim, s);
     if (err != hipSuccess) return hip_status(err, "token-score kernel");
-    err = pd::launch_head_sum_rank(a.part_i, tok_score, tok_rank, a.B, a.N, a.Hq, a.C, a.km_part, key_mean, a.Hkv,
-                                   d->head_dim, km_slots(d), s);
-    if (err != hipSuccess) return hip_status(err, "token-rank kernel");
   } else {
     err = pd::launch_prefill_f32(a, key_mean, d->head_dim, s);
     if (err != hipSuccess) return hip_status(err, "prefill kernel");
     err = pd::launch_escore_f32(e, d->head_dim, s);
     if (err != hipSuccess) return hip_status(err, "token-score kernel");
-    err = pd::launch_head_sum_rank(a.part_i, tok_score, tok_rank, a.B, a.N, a.Hq, a.C, nullptr, nullptr, 0,
-                                   d->head_dim, 0, s);
-    if (err != hipSuccess) return hip_status(err, "token-rank kernel");
   }
-  if (chunk_score) {
-    err = pd::launch_chunk_score(a.qm_mass, chunk_score, a.B, a.N, a.Hq, a.Lq, a.Lm, s);
-    if (err != hipSuccess) return hip_status(err, "chunk-score kernel");
+  pd::RankArgs k{};
+  k.per_head = a.part_i;
+  k.tok_score = tok_score;
+  k.tok_rank = tok_rank;
+  if (bf16) {   // the fp32 prefill writes the means itself
+    k.km_part = a.km_part;
+    k.key_mean = key_mean;
+    k.km_slots = km_slots(d);
   }
+  k.qm_mass = a.qm_mass;
+  k.chunk_score = chunk_score;
+  k.B = a.B;
+  k.N = a.N;
+  k.C = a.C;
+  k.Hq = a.Hq;
+  k.Hkv = a.Hkv;
+  k.D = d->head_dim;
+  k.Lq = a.Lq;
+  k.Lm = a.Lm;
+  err = pd::launch_head_sum_rank(k, s);
+  if (err != hipSuccess) return hip_status(err, "token-rank kernel");
   return ok();
 }
 

@@ -95,13 +95,20 @@ struct JointArgs {
   double rope_base;   // 0: no rotation
 };
 hipError_t launch_gather_joint(const JointArgs& a, hipStream_t s);
-// e = sum over the H_q heads of the per-head sums (fixed order), then the ranks; key means from the partial
-// sums of the cache-writing workgroups (Hkv = 0: none).
-hipError_t launch_head_sum_rank(const float* per_head, float* tok_score, int32_t* tok_rank, int B, int N, int Hq,
-                                int C, const float* km_part, float* key_mean, int Hkv, int D, int km_slots,
-                                hipStream_t s);
-hipError_t launch_chunk_score(const float* qm_mass, float* chunk_score, int B, int N, int Hq, int Lq, int Lm,
-                              hipStream_t s);
+// The end of the prefill: e = sum over the H_q heads of the per-head sums (fixed
+// order) and the ranks; the key means from the partial sums of the cache-writing
+// workgroups (key_mean NULL: none); the chunk scores (chunk_score NULL: none).
+struct RankArgs {
+  const float* per_head;   // [B][N][Hq][C]
+  float* tok_score;
+  int32_t* tok_rank;
+  const float* km_part;    // [B][N][Hkv][km_slots][D]
+  float* key_mean;
+  const float* qm_mass;    // [B][N][Hq][Lq+Lm]
+  float* chunk_score;
+  int B, N, C, Hq, Hkv, D, km_slots, Lq, Lm;
+};
+hipError_t launch_head_sum_rank(const RankArgs& a, hipStream_t s);
 hipError_t launch_select_ranked(const float* chunk_score, int lowest, const int32_t* tok_rank, int32_t* chunk_idx,
                                 int32_t* tok_slot, int B, int N, int C, int K, int Bt, hipStream_t s);
 int select_row_splits(int Ld);

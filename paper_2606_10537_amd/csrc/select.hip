@@ -3,6 +3,8 @@
 //
 //   head_sum_rank: grid (b, n)  -- Eq. 5 scores summed over the heads, bitonic sort
 //                                  in LDS (score desc, index asc) -> token ranks;
+//                                  beside it the key means and, from the content mass
+//                                  of the q/m rows, the prefill-time chunk score;
 //   qscore:     grid (b, h, sp) -- by linearity the chunk score splits into
 //                                  terms scale * <(1/L_d) sum_{r in sp} q_r, kbar_n>
 //                                  over heads and row splits: one workgroup sums
@@ -10,8 +12,6 @@
 //                                  key means of that head's KV group;
 //   gather:     grid (rows)     -- static-selection mode: kept rows copied once
 //                                  into a contiguous per-(sequence, KV head) buffer;
-//   chunk_score: grid (b, n)    -- prefill-time chunk score from the content
-//                                  mass of the query and pseudo-label rows;
 //   select:     grid (b, k)     -- sums the terms of every chunk in a fixed
 //                                  order, ranks the N scores (bitonic sort in
 //                                  LDS), takes the k-th kept chunk in ascending
@@ -73,77 +73,147 @@ static int next_pow2(int x) {
   return p;
 }
 
-// Ascending bitonic sort of P (power of two) keys in LDS by NT threads.
-template <int NT>
-__device__ void bitonic_sort_nt(uint64_t* keys, int P) {
+// Bitonic sort of P = 2^x <= 1024 E keys by 1024 threads; thread t holds keys
+// e * 1024 + t, e < E.  Exchanges over less than a wave go by lane shuffles, those
+// over 1024 and more stay in the thread, and only the others (10 of the 55 stages at
+// 1024 keys) go through LDS, in two buffers of 1024 E keys in turn, so that each
+// needs one barrier.
+constexpr int kRankThreads = 1024;
+template <int E>
+__device__ __forceinline__ void sort_keys(uint64_t (&key)[E], uint64_t* lds, int P) {
+  const int t = threadIdx.x;
+  int buf = 0;
   for (int k = 2; k <= P; k <<= 1) {
     for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = threadIdx.x; i < P; i += NT) {
-        const int ixj = i ^ j;
-        if (ixj > i) {
-          const uint64_t a = keys[i], c = keys[ixj];
-          const bool up = (i & k) == 0;
-          if ((a > c) == up) {
-            keys[i] = c;
-            keys[ixj] = a;
-          }
+      uint64_t other[E];
+      if (j >= kRankThreads) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          other[e] = key[e];
+#pragma unroll
+          for (int x = 0; x < E; ++x)
+            if (x == (e ^ (j / kRankThreads))) other[e] = key[x];
+        }
+      } else if (j >= 64) {
+        uint64_t* const at = lds + buf * (E * kRankThreads);
+        buf ^= 1;
+#pragma unroll
+        for (int e = 0; e < E; ++e) at[e * kRankThreads + t] = key[e];
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < E; ++e) other[e] = at[e * kRankThreads + (t ^ j)];
+      } else {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const uint32_t lo = __shfl_xor((uint32_t)key[e], j), hi = __shfl_xor((uint32_t)(key[e] >> 32), j);
+          other[e] = ((uint64_t)hi << 32) | lo;
         }
       }
-      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int i = e * kRankThreads + t;
+        const bool small = ((i & j) == 0) == ((i & k) == 0);   // this place takes the smaller key
+        key[e] = (other[e] < key[e]) == small ? other[e] : key[e];
+      }
     }
   }
 }
 
-// Workgroups (b*N + n, 0): e of one chunk = sum over the H_q heads of the
-// per-head sums (heads in ascending order), written out, then every
-// token's rank from a sort by 1024 threads (one compare per thread per
-// stage at C = 1024).  Workgroups (b*N + n, y >= 1): the chunk's key means
-// k-bar[g][d] = (1/C) * the sum of the km_slots partial sums of the
-// cache-writing workgroups (fixed order); these workgroups (at most 64 per
-// chunk) take 1024 of the H_kv*d values at a time.
-constexpr int kRankThreads = 1024;
-__global__ __launch_bounds__(kRankThreads) void head_sum_rank_kernel(const float* per_head, float* tok_score,
-                                                                      int32_t* tok_rank, int Hq, int C, int Cpad,
-                                                                      const float* km_part, float* key_mean, int HD,
-                                                                      int D, int km_slots) {
-  extern __shared__ __attribute__((aligned(16))) uint64_t keys[];
+// e of one chunk = sum over the H_q heads of the per-head sums (heads in ascending
+// order), written out, then every token's rank.
+template <int E>
+__device__ __forceinline__ void head_sum_rank(const float* ph, float* tok_score, int32_t* tok_rank, int Hq, int C,
+                                              int Cpad, uint64_t* lds) {
+  uint64_t key[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int j = e * kRankThreads + threadIdx.x;
+    key[e] = ~0ull;
+    if (j < C) {
+      float x = 0.f;
+#pragma unroll 16
+      for (int h = 0; h < Hq; ++h) x += ph[(size_t)h * C + j];
+      tok_score[j] = x;
+      key[e] = rank_key(x, j);
+    }
+  }
+  sort_keys<E>(key, lds, Cpad);
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int i = e * kRankThreads + threadIdx.x;
+    if (i < C) tok_rank[(uint32_t)key[e]] = i;
+  }
+}
+
+// Prefill-time chunk score of one (b, n) from the per-head content masses of its
+// L_q + L_m query and pseudo-label rows: a(r) = (1/H_q) sum_h mass[h][r],
+// s = -(1/L_q) sum_{r < L_q} ln a(r) - (1/L_m) sum_{r >= L_q} ln a(r) (the
+// second term only when L_m > 0).  Thread t takes rows t, t + 1024, ...; both
+// sums are reduced by a fixed tree, so the result is reproducible.
+__device__ __forceinline__ void chunk_score_sum(const float* m, float* chunk_score, int Hq, int Lq, int Lm,
+                                                float* red) {
+  const int R = Lq + Lm, t = threadIdx.x;
+  float si = 0.f, sp = 0.f;
+  for (int r = t; r < R; r += kRankThreads) {
+    float a = 0.f;
+#pragma unroll 16
+    for (int h = 0; h < Hq; ++h) a += m[(size_t)h * R + r];
+    const float nl = -logf(a / Hq);
+    if (r < Lq) si += nl;
+    else sp += nl;
+  }
+  red[t] = si;
+  red[kRankThreads + t] = sp;
+  __syncthreads();
+  for (int w = kRankThreads / 2; w > 0; w >>= 1) {
+    if (t < w) {
+      red[t] += red[t + w];
+      red[kRankThreads + t] += red[kRankThreads + t + w];
+    }
+    __syncthreads();
+  }
+  if (t == 0) *chunk_score = red[0] / Lq + (Lm > 0 ? red[kRankThreads] / Lm : 0.f);
+}
+
+// The end of the prefill, one chunk per blockIdx.x.  y = 0: token scores and ranks.
+// y = 1: the chunk score, if asked for.  The others, at most 64: the key means
+// k-bar[g][d] = (1/C) * the sum of the km_slots partial sums of the cache-writing
+// workgroups (fixed order), 1024 of the H_kv*d values at a time.  With every sort
+// stage in LDS behind a barrier and the chunk score in a launch of its own, one load
+// after the other, the two took 20 and 21 us at 16K; this way the whole prefill of
+// 16K went from 539 to 512 us, of 2 x 5 chunks of 777 from 78.5 to 73.2 us.
+template <int E>
+__global__ __launch_bounds__(kRankThreads) void head_sum_rank_kernel(RankArgs a, int Cpad) {
+  extern __shared__ __attribute__((aligned(16))) uint64_t lds[];
   const size_t bn = blockIdx.x;
-  if (blockIdx.y > 0) {
-    for (int i = (blockIdx.y - 1) * kRankThreads + threadIdx.x; i < HD; i += (gridDim.y - 1) * kRankThreads) {
-      const int g = i / D, d = i % D;
-      const float* src = km_part + ((bn * (HD / D) + g) * (size_t)km_slots) * D + d;
+  const int first_km = a.chunk_score ? 2 : 1;
+  if ((int)blockIdx.y >= first_km) {
+    const int HD = a.Hkv * a.D, n_km = gridDim.y - first_km;
+    for (int i = (blockIdx.y - first_km) * kRankThreads + threadIdx.x; i < HD; i += n_km * kRankThreads) {
+      const int g = i / a.D, d = i % a.D;
+      const float* src = a.km_part + ((bn * a.Hkv + g) * (size_t)a.km_slots) * a.D + d;
       float sum = 0.f;
 #pragma unroll 8
-      for (int q = 0; q < km_slots; ++q) sum += src[(size_t)q * D];
-      key_mean[bn * HD + i] = sum * (1.0f / C);
+      for (int q = 0; q < a.km_slots; ++q) sum += src[(size_t)q * a.D];
+      a.key_mean[bn * HD + i] = sum * (1.0f / a.C);
     }
-    return;
+  } else if (blockIdx.y == 1) {
+    chunk_score_sum(a.qm_mass + bn * a.Hq * (a.Lq + a.Lm), a.chunk_score + bn, a.Hq, a.Lq, a.Lm,
+                    reinterpret_cast<float*>(lds));
+  } else {
+    head_sum_rank<E>(a.per_head + bn * a.Hq * a.C, a.tok_score + bn * a.C, a.tok_rank + bn * a.C, a.Hq, a.C, Cpad,
+                     lds);
   }
-  const float* ph = per_head + bn * Hq * C;
-  for (int j = threadIdx.x; j < Cpad; j += kRankThreads) {
-    if (j < C) {
-      float e = 0.f;
-#pragma unroll 16
-      for (int h = 0; h < Hq; ++h) e += ph[(size_t)h * C + j];
-      tok_score[bn * C + j] = e;
-      keys[j] = rank_key(e, j);
-    } else {
-      keys[j] = ~0ull;
-    }
-  }
-  __syncthreads();
-  bitonic_sort_nt<kRankThreads>(keys, Cpad);
-  for (int i = threadIdx.x; i < C; i += kRankThreads) tok_rank[bn * C + (uint32_t)keys[i]] = i;
 }
 
-hipError_t launch_head_sum_rank(const float* per_head, float* tok_score, int32_t* tok_rank, int B, int N, int Hq,
-                                int C, const float* km_part, float* key_mean, int Hkv, int D, int km_slots,
-                                hipStream_t s) {
-  const int Cpad = next_pow2(C);
-  const int HD = Hkv * D;
-  const dim3 grid(B * N, 1 + std::min(64, (HD + kRankThreads - 1) / kRankThreads));
-  hipLaunchKernelGGL(head_sum_rank_kernel, grid, dim3(kRankThreads), (size_t)Cpad * 8, s, per_head, tok_score,
-                     tok_rank, Hq, C, Cpad, km_part, key_mean, HD, D, km_slots);
+hipError_t launch_head_sum_rank(const RankArgs& a, hipStream_t s) {
+  const int Cpad = next_pow2(a.C);
+  const int n_km = a.key_mean ? std::min(64, (a.Hkv * a.D + kRankThreads - 1) / kRankThreads) : 0;
+  const dim3 grid(a.B * a.N, 1 + (a.chunk_score ? 1 : 0) + n_km);
+  const size_t bytes = 2 * 8 * (size_t)std::max(Cpad, kRankThreads);   // two buffers of the sort
+  if (Cpad <= 1024) hipLaunchKernelGGL(head_sum_rank_kernel<1>, grid, dim3(kRankThreads), bytes, s, a, Cpad);
+  else if (Cpad <= 2048) hipLaunchKernelGGL(head_sum_rank_kernel<2>, grid, dim3(kRankThreads), bytes, s, a, Cpad);
+  else hipLaunchKernelGGL(head_sum_rank_kernel<4>, grid, dim3(kRankThreads), bytes, s, a, Cpad);
   return hipGetLastError();
 }
 
@@ -379,44 +449,6 @@ hipError_t launch_select_ranked(const float* chunk_score, int lowest, const int3
   const int Npad = next_pow2(N);
   hipLaunchKernelGGL(select_kernel, dim3(B * K), dim3(256), (size_t)Npad * 8, s, chunk_score, tok_rank,
                      (float*)nullptr, chunk_idx, tok_slot, N, C, K, Bt, 1, Npad, lowest);
-  return hipGetLastError();
-}
-
-// Prefill-time chunk score of one (b, n) from the per-head content masses of
-// its L_q + L_m query and pseudo-label rows: a(r) = (1/H_q) sum_h mass[h][r],
-// s = -(1/L_q) sum_{r < L_q} ln a(r) - (1/L_m) sum_{r >= L_q} ln a(r) (the
-// second term only when L_m > 0).  Thread t takes rows t, t + 256, ...; both
-// sums are reduced by a fixed tree, so the result is reproducible.
-__global__ __launch_bounds__(256) void chunk_score_kernel(const float* qm_mass, float* chunk_score, int Hq, int Lq,
-                                                           int Lm) {
-  __shared__ float red[2][256];
-  const size_t bn = blockIdx.x;
-  const int R = Lq + Lm, t = threadIdx.x;
-  const float* m = qm_mass + bn * Hq * R;
-  float si = 0.f, sp = 0.f;
-  for (int r = t; r < R; r += 256) {
-    float a = 0.f;
-    for (int h = 0; h < Hq; ++h) a += m[(size_t)h * R + r];
-    const float nl = -logf(a / Hq);
-    if (r < Lq) si += nl;
-    else sp += nl;
-  }
-  red[0][t] = si;
-  red[1][t] = sp;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (t < w) {
-      red[0][t] += red[0][t + w];
-      red[1][t] += red[1][t + w];
-    }
-    __syncthreads();
-  }
-  if (t == 0) chunk_score[bn] = red[0][0] / Lq + (Lm > 0 ? red[1][0] / Lm : 0.f);
-}
-
-hipError_t launch_chunk_score(const float* qm_mass, float* chunk_score, int B, int N, int Hq, int Lq, int Lm,
-                              hipStream_t s) {
-  hipLaunchKernelGGL(chunk_score_kernel, dim3(B * N), dim3(256), 0, s, qm_mass, chunk_score, Hq, Lq, Lm);
   return hipGetLastError();
 }
 

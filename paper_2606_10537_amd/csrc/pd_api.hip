@@ -35,7 +35,7 @@ constexpr int kMaxChunks = 1024;
 constexpr int kMaxChunkLen = 4096;
 constexpr int kMaxSplits = 64;
 constexpr int kMaxCompactRows = 1 << 20;   // prefix rows of a compact decode call
-constexpr int kTargetWorkgroups = 512;   // two resident workgroups of four waves on 256 CUs
+constexpr int kNumCu = 256;
 constexpr size_t kAlign = 256;
 
 size_t round_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
@@ -143,9 +143,15 @@ pd_status check_select_grid(const pd_dims* d, int rows) {
 }
 
 // Shard counts for a decode call whose KV has n_sel prefix rows per (sequence,
-// KV head) ahead of the static and own rows.  Requested count: explicit, or
-// chosen so that the decode grid fills the CUs while every shard keeps >= 4 KV
-// tiles of 64 rows.  The bf16 kernel also needs every shard to fit its LDS row
+// KV head) ahead of the static and own rows.  Requested count: explicit, or, for
+// bf16, as many as keep one workgroup per CU (a CU with two takes longer than
+// any with one: 8K batch 1, 64 row tiles, takes 23.1 us with 4 shards and 26.0
+// with 5) and no more than 2 sqrt(tiles), where shorter sweeps no longer pay
+// for the larger merge (10 tiles, 16 rows: 11.3 us with 6 shards, 14.6 with 2,
+// 16.8 with 1; 66 tiles, 32 rows: 20.4 us with 12, 20.7 with 16, 22.7 with 32,
+// and, with the keys not in cache, the step takes 28.0 us with 16, 29.5 with 13).
+// Below 8 tiles the merge costs more than it saves (a step over 6 tiles: 20.5 us
+// with 1 shard, 23.9 with 4).  fp32 shards keep >= 4 tiles of 64 rows.  The bf16 kernel also needs every shard to fit its LDS row
 // table (at most kDecodeTableRows rows, i.e. kDecodeTableRows/64 tiles),
 // whatever n_static is.
 int min_splits(const pd_dims* d, long long n_sel) {
@@ -157,10 +163,13 @@ int min_splits(const pd_dims* d, long long n_sel) {
 int requested_splits(const pd_dims* d, long long n_sel, int num_splits) {
   int s = num_splits;
   if (s <= 0) {
-    const long long lkv0 = n_sel + d->dec_len;
-    const int max_by_len = std::max(1, cdiv(lkv0, 64) / 4);
-    const int want = cdiv(kTargetWorkgroups, std::max(1LL, decode_units(d)));
-    s = std::max(1, std::min(std::min(want, max_by_len), kMaxSplits));
+    const int tiles = cdiv(n_sel + d->dec_len, 64);
+    const long long units = std::max(1LL, decode_units(d));
+    if (d->dtype == PD_BF16)
+      s = tiles < 8 ? 1 : (int)std::min(kNumCu / units, (long long)std::ceil(2.0 * std::sqrt((double)tiles)));
+    else
+      s = std::min(cdiv(kNumCu, units), tiles / 4);
+    s = std::max(1, std::min(s, kMaxSplits));
   }
   return std::max(s, min_splits(d, n_sel));
 }

@@ -346,9 +346,26 @@ __device__ void chunk_keys(const float* partial, int b, int N, int T, int Npad, 
   __syncthreads();
 }
 
+// Sum of the values of all lower threads of 256 (within each wave by shuffles, then
+// across the 4 waves through wsum).
+__device__ __forceinline__ int block_exclusive_sum(int x, int* wsum) {
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  int inc = x;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(inc, o);
+    if (lane >= o) inc += y;
+  }
+  if (lane == 63) wsum[wv] = inc;
+  __syncthreads();
+  int pos = inc - x;
+  for (int w = 0; w < wv; ++w) pos += wsum[w];
+  return pos;
+}
+
 // Kept tokens (rank < Bt) of one chunk in ascending order: counts over
-// contiguous segments, an exclusive scan (within each wave by shuffles, then
-// across the 4 waves), then each segment writes its slots (token + 1).  The
+// contiguous segments, an exclusive scan, then each segment writes its slots
+// (token + 1).  The
 // ranks of a segment are loaded 16 at a time, all in flight before the first
 // compare (a plain loop waits for each load in turn).
 __device__ void list_tokens(const int32_t* rk, int C, int Bt, int32_t* out, int* wsum) {
@@ -364,17 +381,7 @@ __device__ void list_tokens(const int32_t* rk, int C, int Bt, int32_t* out, int*
 #pragma unroll
     for (int u = 0; u < U; ++u) cnt += r[u] < Bt;
   }
-  const int lane = t & 63, wv = t >> 6;
-  int inc = cnt;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(inc, o);
-    if (lane >= o) inc += y;
-  }
-  if (lane == 63) wsum[wv] = inc;
-  __syncthreads();
-  int pos = inc - cnt;
-  for (int w = 0; w < wv; ++w) pos += wsum[w];
+  int pos = block_exclusive_sum(cnt, wsum);
   for (int base = j0; base < j1; base += U) {
     int r[U];
 #pragma unroll
@@ -383,6 +390,49 @@ __device__ void list_tokens(const int32_t* rk, int C, int Bt, int32_t* out, int*
     for (int u = 0; u < U; ++u)
       if (r[u] < Bt) out[pos++] = base + u + 1;
   }
+}
+
+// The same for at most 64 chunks: one workgroup per (sequence, chunk n) loads the
+// ranks of its own chunk while it waits for the scores, finds out whether the chunk
+// is kept and where, and lists its tokens: one dependent trip to memory less than
+// when the chunk is known first (steps: 8K 30.2 -> 29.8 us, 16K 30.4 -> 29.3, 32-row
+// block 27.8 -> 26.7).  More chunks: every workgroup sums all scores, so K of them do.
+constexpr int kSelectAll = 64;
+__global__ __launch_bounds__(256) void select_all_kernel(const float* partial, const int32_t* tok_rank,
+                                                          float* chunk_score, int32_t* chunk_idx, int32_t* tok_slot,
+                                                          int N, int C, int K, int Bt, int T, int neg) {
+  constexpr int U = 16;   // tokens of a thread: C <= 4096
+  __shared__ uint64_t keys[kSelectAll];
+  __shared__ int wsum[4];
+  __shared__ int my_pos;
+  const int b = blockIdx.x / N, n = blockIdx.x % N;
+  const int t = threadIdx.x;
+  const int32_t* rk = tok_rank + ((size_t)b * N + n) * C;
+  const int seg = (C + 255) / 256;
+  const int j0 = min(C, t * seg), j1 = min(C, j0 + seg);
+  int r[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) r[u] = j0 + u < j1 ? rk[j0 + u] : Bt;
+  chunk_keys(partial, b, N, T, kSelectAll, neg, keys, n == 0 ? chunk_score : nullptr);
+  if (t < 64) {
+    const uint64_t me = keys[t];
+    int rank = 0;
+    for (int i = 0; i < N; ++i) rank += keys[i] < me;
+    const uint64_t kept = __ballot(t < N && rank < K);
+    if (t == n) my_pos = (kept >> n) & 1 ? __popcll(kept & ((1ull << n) - 1)) : -1;
+  }
+  __syncthreads();
+  const int k = my_pos;
+  if (k < 0) return;
+  if (t == 0) chunk_idx[(size_t)b * K + k] = n;
+  int cnt = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) cnt += r[u] < Bt;
+  int pos = block_exclusive_sum(cnt, wsum);
+  int32_t* out = tok_slot + ((size_t)b * K + k) * Bt;
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (r[u] < Bt) out[pos++] = j0 + u + 1;
 }
 
 // neg = 1 keeps the K lowest scores instead of the K highest.  One workgroup
@@ -426,9 +476,23 @@ __global__ __launch_bounds__(256) void select_kernel(const float* partial, const
   list_tokens(tok_rank + ((size_t)b * N + my_chunk) * C, C, Bt, tok_slot + ((size_t)b * K + k) * Bt, wsum);
 }
 
+// Selection from T score terms per chunk.
+static hipError_t launch_select(const float* partial, const int32_t* tok_rank, float* chunk_score, int32_t* chunk_idx,
+                                int32_t* tok_slot, int B, int N, int C, int K, int Bt, int T, int neg,
+                                hipStream_t s) {
+  if (N <= kSelectAll) {
+    hipLaunchKernelGGL(select_all_kernel, dim3(B * N), dim3(256), 0, s, partial, tok_rank, chunk_score, chunk_idx,
+                       tok_slot, N, C, K, Bt, T, neg);
+  } else {
+    const int Npad = next_pow2(N);
+    hipLaunchKernelGGL(select_kernel, dim3(B * K), dim3(256), (size_t)Npad * 8, s, partial, tok_rank, chunk_score,
+                       chunk_idx, tok_slot, N, C, K, Bt, T, Npad, neg);
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_score_select(const SelectArgs& a, hipStream_t s) {
   const dim3 g1(a.B * a.Hq * a.NS);
-  const int Npad = next_pow2(a.N);
 #define PD_QSCORE(BF, DD) hipLaunchKernelGGL((qscore_kernel<BF, DD>), g1, dim3(256), 0, s, a)
   if (a.D == 128) {
     if (a.bf16) PD_QSCORE(true, 128); else PD_QSCORE(false, 128);
@@ -438,18 +502,14 @@ hipError_t launch_score_select(const SelectArgs& a, hipStream_t s) {
 #undef PD_QSCORE
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(select_kernel, dim3(a.B * a.K), dim3(256), (size_t)Npad * 8, s, a.partial, a.tok_rank,
-                     a.chunk_score, a.chunk_idx, a.tok_slot, a.N, a.C, a.K, a.Bt, a.Hq * a.NS, Npad, 0);
-  return hipGetLastError();
+  return launch_select(a.partial, a.tok_rank, a.chunk_score, a.chunk_idx, a.tok_slot, a.B, a.N, a.C, a.K, a.Bt,
+                       a.Hq * a.NS, 0, s);
 }
 
 // Selection from scores the caller supplies (one term per chunk).
 hipError_t launch_select_ranked(const float* chunk_score, int lowest, const int32_t* tok_rank, int32_t* chunk_idx,
                                 int32_t* tok_slot, int B, int N, int C, int K, int Bt, hipStream_t s) {
-  const int Npad = next_pow2(N);
-  hipLaunchKernelGGL(select_kernel, dim3(B * K), dim3(256), (size_t)Npad * 8, s, chunk_score, tok_rank,
-                     (float*)nullptr, chunk_idx, tok_slot, N, C, K, Bt, 1, Npad, lowest);
-  return hipGetLastError();
+  return launch_select(chunk_score, tok_rank, nullptr, chunk_idx, tok_slot, B, N, C, K, Bt, 1, lowest, s);
 }
 
 // Static-selection mode: copy the kept rows of every (sequence, KV head) into a

@@ -56,3 +56,15 @@ def test_decode_tiles(case):
     o, lse = run_decode(d, K, Bt, dec, cache, ci, ts, x["k_qm"], x["v_qm"], ns, num_splits=S)
     torch.cuda.synchronize()
     decode_check(d, K, Bt, dec, cache, ci, ts, x["k_qm"], x["v_qm"], ns, o, lse, batches=[0, B - 1])
+
+
+@pytest.mark.parametrize("C", [1, 63, 1024, 1025, 2049, 4096])
+def test_rank_sort_sizes(C):
+    """Token ranks where the sort's threads hold one, two and four keys."""
+    d = Dims(1, 2, C, 3, 2, 4, 2, 1, 64, PD_FP32)
+    out = run_prefill(d, random_prefill_inputs(d, seed=C, scale=0.125), chunk_score=True)
+    torch.cuda.synchronize()
+    e, rank = out["tok_score"].cpu(), out["tok_rank"].cpu().long()
+    order = torch.sort(e, dim=2, descending=True, stable=True)[1]
+    want = torch.empty_like(order).scatter_(2, order, torch.arange(C).expand(1, 2, C).contiguous())
+    assert torch.equal(rank, want)

@@ -1,0 +1,54 @@
+"""Selection where its kernels change over: 64 and 65 chunks, one token and 4096 (one and 16 a thread), all
+and one kept, equal scores.  Whole numbers: compared exactly."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_path import run_select
+from paper_2606_10537_amd import _lib
+from paper_2606_10537_amd._lib import PD_FP32, Dims
+
+pytestmark = pytest.mark.gpu
+
+# B, N, C, K, Bt
+CASES = [(1, 1, 1, 1, 1), (2, 63, 17, 63, 5), (3, 64, 256, 1, 256), (2, 64, 257, 64, 1), (2, 65, 257, 65, 100),
+         (1, 65, 40, 2, 40), (1, 4, 4096, 3, 4095), (2, 3, 1025, 2, 511)]
+
+
+@pytest.mark.parametrize("lowest", [0, 1])
+@pytest.mark.parametrize("case", CASES, ids=[str(c) for c in CASES])
+def test_select_ranked_edges(case, lowest):
+    B, N, C, K, Bt = case
+    d = Dims(B, N, C, 4, 0, 8, 2, 1, 64, PD_FP32)
+    g = torch.Generator().manual_seed(N * C)
+    # Scores in steps of 1/4: many equal ones, the lower index first.
+    s = torch.randint(-6, 7, (B, N), generator=g).float() / 4
+    rank = torch.argsort(torch.rand((B, N, C), generator=g), dim=2).to(torch.int32)
+    ci = torch.full((B, K), -1, dtype=torch.int32, device="cuda")
+    ts = torch.full((B, K, Bt), -1, dtype=torch.int32, device="cuda")
+    _lib.pd_select_ranked(d, K, Bt, s.cuda(), lowest, rank.cuda(), ci, ts)
+    torch.cuda.synchronize()
+    order = np.argsort(s.numpy() if lowest else -s.numpy(), axis=1, kind="stable")
+    want = np.sort(order[:, :K], axis=1)
+    assert np.array_equal(ci.cpu().numpy(), want)
+    assert np.array_equal(ts.cpu().numpy(), oracle.tokens_by_rank_ref(rank.numpy(), want, Bt))
+
+
+@pytest.mark.parametrize("N", [64, 65])
+def test_score_select_both_kernels(N):
+    """The same sequence's chunks with and without one more: the scores and the kept sets agree."""
+    d = Dims(2, N, 33, 4, 0, 40, 4, 2, 64, PD_FP32)
+    g = torch.Generator().manual_seed(9)
+    q = torch.randn((2, 40, 4, 64), generator=g).cuda()
+    km = torch.randn((2, 65, 2, 64), generator=g)
+    km[:, 64] = -km[:, :64].mean(dim=1)
+    rank = torch.argsort(torch.rand((2, 65, 33), generator=g), dim=2).to(torch.int32)
+    ci, ts, cs = run_select(d, 5, 9, q, km[:, :N].contiguous().cuda(), rank[:, :N].contiguous().cuda())
+    torch.cuda.synchronize()
+    ref = oracle.chunk_scores_ref(q.cpu().double().numpy(), km[:, :N].double().numpy())
+    np.testing.assert_allclose(cs.cpu().double().numpy(), ref, rtol=1e-5, atol=1e-5)
+    want = np.sort(np.argsort(-ref, axis=1, kind="stable")[:, :5], axis=1)
+    assert np.array_equal(ci.cpu().numpy(), want)
+    assert np.array_equal(ts.cpu().numpy(), oracle.tokens_by_rank_ref(rank[:, :N].numpy(), want, 9))

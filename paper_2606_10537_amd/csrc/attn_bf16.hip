@@ -35,6 +35,7 @@
 // m of the 4 elements read by lane 4m + j/4, element j % 4.  If lane k of the
 // group points at V[key0 + k/4][d0 + 4(k%4)], lane j therefore receives
 // V[key0 + m][d0 + j], m = 0..3: four consecutive keys of one column.
+#include <algorithm>
 #include <utility>
 
 #include "pd_common.h"
@@ -987,10 +988,10 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_bf16_kernel(DecodeArgs p) {
 }
 
 // ---------------------------------------------------------------------------
-// Eq. 5, first sum, one workgroup per (b, n, h): the query rows of head h and
+// Eq. 5, first sum, blockIdx.x = (b, n, h): the query rows of head h and
 // their final LSE are staged in LDS (up to 128 rows per pass), and the 4 waves
-// split the C content keys in 32-key blocks, so every key row is read from HBM
-// once.  S = Q_q K_c^T on MFMA (A: query rows from LDS, B: key rows from
+// of each of gridDim.y workgroups split the C content keys in 32-key blocks, so every
+// key row is read from HBM once.  S = Q_q K_c^T on MFMA (A: query rows from LDS, B: key rows from
 // global memory, the next block's prefetched), each key's mass exp2(S*scale -
 // lse2(row)) summed in the lane that holds the key.  The head's sum is added
 // in place to its per-head second sum (written by the prefill), or replaces
@@ -1032,9 +1033,10 @@ __global__ __launch_bounds__(256) void escore2_bf16_kernel(EscoreArgs p) {
     for (int r = tid; r < QB; r += 256) ls[r] = r < nr ? lse[r0 + r] : INFINITY;
     __syncthreads();
     bf16x8 kf[KS], kn[KS];
-    if (wave < nkb) load_k(wave, kf);
-    for (int kb = wave; kb < nkb; kb += 4) {
-      if (kb + 4 < nkb) load_k(kb + 4, kn);
+    const int kb0 = blockIdx.y * 4 + wave, step = 4 * gridDim.y;
+    if (kb0 < nkb) load_k(kb0, kf);
+    for (int kb = kb0; kb < nkb; kb += step) {
+      if (kb + step < nkb) load_k(kb + step, kn);
       float colsum = 0.f;
 #pragma unroll
       for (int qb = 0; qb < QB / 32; ++qb) {
@@ -1057,7 +1059,7 @@ __global__ __launch_bounds__(256) void escore2_bf16_kernel(EscoreArgs p) {
       const float v = colsum + __shfl_xor(colsum, 32);
       const int j = kb * 32 + l32;
       if (grp == 0 && j < p.C) ph[j] = (p.q2c && r0 == 0) ? v : ph[j] + v;
-      if (kb + 4 < nkb) {
+      if (kb + step < nkb) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) kf[ks] = kn[ks];
       }
@@ -1106,9 +1108,18 @@ hipError_t launch_decode_bf16(const DecodeArgs& a, int head_dim, hipStream_t s) 
   return head_dim == 128 ? launch_decode_d<128>(a, s) : launch_decode_d<64>(a, s);
 }
 
+// Workgroups up to which the keys of a head are split in the token scores.  With
+// one workgroup a head few chunks leave each SIMD one wave, which waits for its own
+// keys, MFMAs and exponentials in turn: 120 heads of d = 64 take 13.0 us in one piece
+// and 7.6 in seven, 256 of d = 128 22 and 19 in four, 448 27 and 26 in two.  Every
+// workgroup stages the query rows again, so up to 2048 of them cost more (22 us for
+// 256 heads, 28 for 448).
+constexpr int kEscoreGroups = 1024;
 template <int D>
 static hipError_t launch_escore_d(const EscoreArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(escore2_bf16_kernel<D>, dim3(a.B * a.N * a.Hq), dim3(256), 0, s, a);
+  const long long heads = (long long)a.B * a.N * a.Hq;
+  const int splits = (int)std::max(1LL, std::min<long long>(((a.C + 31) / 32 + 3) / 4, kEscoreGroups / heads));
+  hipLaunchKernelGGL(escore2_bf16_kernel<D>, dim3((unsigned)heads, splits), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 hipError_t launch_escore_bf16(const EscoreArgs& a, int head_dim, hipStream_t s) {

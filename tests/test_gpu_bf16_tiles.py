@@ -43,7 +43,9 @@ def test_decode_tiles(case):
 
 # C, Lq, Lm, D: chunk sequences of 1 + C + Lq + Lm rows
 PREFILL = [(63, 1, 0, 128), (62, 1, 0, 64), (64, 63, 0, 128), (63, 64, 1, 64), (126, 1, 0, 128), (127, 1, 0, 128),
-           (70, 190, 3, 64)]
+           (70, 190, 3, 64),
+           # token scores with the keys of a head split: 4 blocks of 32 a workgroup, 1 in the last; two passes
+           (513, 5, 0, 128), (300, 190, 3, 64)]
 
 
 @pytest.mark.parametrize("case", PREFILL, ids=[str(c) for c in PREFILL])

@@ -163,8 +163,8 @@ struct FragAddr {
 };
 
 // One KV tile for one wave: S^T = K Q^T, online softmax producing the bf16
-// weights P, O^T += V^T P^T.  kv_valid: number of valid keys in this tile (64
-// except in a ragged last tile).  mr: keys counted into qmass.  EXACT: also keep
+// weights P, O^T += V^T P^T.  KEYS: keys that are computed, 64 or kShortTile.
+// kv_valid: number of valid keys among them (KEYS except in a ragged last tile).  mr: keys counted into qmass.  EXACT: also keep
 // the unrounded row sum and the counted mass (prefill).  O is normalised by the
 // sum of the same bf16-rounded weights that multiply V, so rounding P perturbs a
 // convex combination instead of scaling O.
@@ -196,24 +196,23 @@ __device__ __forceinline__ float max_across_halves(float x) {
 // -m (log2 domain) for the exponent FMA.  Key of s[kb][r]: 32*kb + 8*(r/4) +
 // 4*grp + r%4.  The max is taken on raw scores (the scale is positive) and the
 // scale is folded into one FMA: p = exp2(s * scale_log2 - m).
-template <int D, bool EXACT>
+template <int D, bool EXACT, int KEYS>
 __device__ __forceinline__ float softmax_max(WaveState<D>& st, f32x16 (&s)[2], int grp, float scale_log2,
                                              int kv_valid) {
   using T = Tile<D>;
-  if (__builtin_expect(kv_valid < 64, 0)) {
+  if (KEYS < 64 || __builtin_expect(kv_valid < 64, 0)) {
     const int valid = kv_valid - 4 * opaque(grp);
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[kb][r] = 32 * kb + 8 * (r >> 2) + (r & 3) < valid ? s[kb][r] : -INFINITY;
+    for (int e = 0; e < KEYS / 2; ++e) {
+      const int kb = e >> 4, r = e & 15;
+      s[kb][r] = 32 * kb + 8 * (r >> 2) + (r & 3) < valid ? s[kb][r] : -INFINITY;
+    }
   }
   // One v_max3_f32 per pair (the file is built without NaN semantics, so no
   // canonicalising v_max precedes each score).
   float mx = -INFINITY;
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) mx = fmaxf(fmaxf(mx, s[kb][r]), s[kb][r + 1]);
+  for (int e = 0; e < KEYS / 2; e += 2) mx = fmaxf(fmaxf(mx, s[e >> 4][e & 15]), s[e >> 4][(e & 15) + 1]);
   mx = max_across_halves(mx) * scale_log2;
   const bool upd = mx > st.m + 8.0f;
   if (__builtin_expect(__ballot(upd) != 0, 0)) {
@@ -239,7 +238,7 @@ __device__ __forceinline__ float softmax_max(WaveState<D>& st, f32x16 (&s)[2], i
 // returned.  COUNT: cnt receives the sum over keys [qlo, qhi).  The first VP
 // fragments of the tile's V are read on the way: they land behind the
 // exponentials and wait in registers for the P*V of the next phase.
-template <int D, bool EXACT, bool COUNT>
+template <int D, bool EXACT, bool COUNT, int KEYS>
 __device__ __forceinline__ float softmax_exp(const f32x16 (&s)[2], uint32_t (&pk)[16], bf16x8 (&vf)[Tile<D>::NF],
                                              const uint16_t* Vs, const FragAddr& fa, float nm, float scale_log2,
                                              int grp, int qlo, int qhi, float& cnt) {
@@ -251,7 +250,7 @@ __device__ __forceinline__ float softmax_exp(const f32x16 (&s)[2], uint32_t (&pk
     qhi -= first;
   }
 #pragma unroll
-  for (int g = 0; g < 4; ++g) {
+  for (int g = 0; g < KEYS / 16; ++g) {
     if (g < 2) {
 #pragma unroll
       for (int i = 0; i < Q; ++i) vf[g * Q + i] = v_frag<D>(Vs, fa, g * Q + i);
@@ -282,25 +281,25 @@ __device__ __forceinline__ float softmax_exp(const f32x16 (&s)[2], uint32_t (&pk
 // (EXACT) the row sum and the mass of the lane's counted keys kept.  A range that
 // covers the whole tile takes the tile's exact row sum; the per-key test runs
 // only in tiles where some lane's range is partial.
-template <int D, bool EXACT>
+template <int D, bool EXACT, int KEYS>
 __device__ __forceinline__ void softmax_phase(WaveState<D>& st, f32x16 (&s)[2], uint32_t (&pk)[16],
                                               bf16x8 (&vf)[Tile<D>::NF], const uint16_t* Vs, const FragAddr& fa,
                                               int grp, int lane32, float scale_log2, int kv_valid,
                                               const MassRange& mr) {
-  const float nm = softmax_max<D, EXACT>(st, s, grp, scale_log2, kv_valid);
+  const float nm = softmax_max<D, EXACT, KEYS>(st, s, grp, scale_log2, kv_valid);
   float cnt = 0.f;
   if constexpr (!EXACT) {
-    softmax_exp<D, false, false>(s, pk, vf, Vs, fa, nm, scale_log2, grp, 0, 0, cnt);
+    softmax_exp<D, false, false, KEYS>(s, pk, vf, Vs, fa, nm, scale_log2, grp, 0, 0, cnt);
   } else {
     const bool none = mr.lo0 >= mr.hi0 && mr.lo1 >= mr.hi1;   // wave-uniform: nothing counted in this tile
     const bool first = lane32 < mr.split;
     const int qlo = first ? mr.lo0 : mr.lo1, qhi = first ? mr.hi0 : mr.hi1;
     const bool any = qlo < qhi;
     if (!none && __ballot(any && (qlo > 0 || qhi < 64))) {
-      st.lx += softmax_exp<D, true, true>(s, pk, vf, Vs, fa, nm, scale_log2, grp, qlo, qhi, cnt);
+      st.lx += softmax_exp<D, true, true, KEYS>(s, pk, vf, Vs, fa, nm, scale_log2, grp, qlo, qhi, cnt);
       st.qmass += cnt;
     } else {
-      const float lsum = softmax_exp<D, true, false>(s, pk, vf, Vs, fa, nm, scale_log2, grp, 0, 0, cnt);
+      const float lsum = softmax_exp<D, true, false, KEYS>(s, pk, vf, Vs, fa, nm, scale_log2, grp, 0, 0, cnt);
       st.lx += lsum;
       st.qmass += any ? lsum : 0.f;
     }
@@ -322,17 +321,18 @@ __device__ __forceinline__ void softmax_phase(WaveState<D>& st, f32x16 (&s)[2], 
 // side, but waits for the matrix core: 69 cycles each beside another wave's
 // MFMAs, 5 alone.)
 // NEXT: the second half also reads the first KP fragments of the next K tile.
-template <int D, bool NEXT>
+template <int D, bool NEXT, int KEYS>
 __device__ __forceinline__ void pv_phase(WaveState<D>& st, const uint32_t (&pk)[16], bf16x8 (&vf)[Tile<D>::NF],
                                          bf16x8 (&kf)[Tile<D>::NF], const uint16_t* Vs, const uint16_t* Ks_next,
                                          const FragAddr& fa) {
   using T = Tile<D>;
+  constexpr int NI = T::NF * KEYS / 64;
   const bf16x8 ones = __builtin_bit_cast(bf16x8, u32x4{fa.ones, fa.ones, fa.ones, fa.ones});
 #pragma unroll
-  for (int i = 0; i < T::NF; ++i) {
+  for (int i = 0; i < NI; ++i) {
     const int kk = i / T::DB, db = i % T::DB;
     const bf16x8 pf = __builtin_bit_cast(bf16x8, u32x4{pk[4 * kk], pk[4 * kk + 1], pk[4 * kk + 2], pk[4 * kk + 3]});
-    if (i + T::VP < T::NF) vf[i + T::VP] = v_frag<D>(Vs, fa, i + T::VP);
+    if (i + T::VP < NI) vf[i + T::VP] = v_frag<D>(Vs, fa, i + T::VP);
     if (NEXT && i + T::KP >= T::NF) kf[i + T::KP - T::NF] = k_frag<D>(Ks_next, fa, i + T::KP - T::NF);
     st.o[db] = mfma32x32x16(vf[i], pf, st.o[db]);
     if (db == 0) st.l = mfma16x16x32(ones, pf, st.l);
@@ -341,25 +341,27 @@ __device__ __forceinline__ void pv_phase(WaveState<D>& st, const uint32_t (&pk)[
 }
 
 // The first KP fragments of a K tile.
-template <int D>
+template <int D, int KEYS = 64>
 __device__ __forceinline__ void k_first(bf16x8 (&kf)[Tile<D>::NF], const uint16_t* Ks, const FragAddr& fa) {
 #pragma unroll
-  for (int i = 0; i < Tile<D>::KP; ++i) kf[i] = k_frag<D>(Ks, fa, i);
+  for (int i = 0; i < Tile<D>::KP; i += KEYS > 32 ? 1 : 2) kf[i] = k_frag<D>(Ks, fa, i);
 }
 
 // S^T of a tile whose first KP fragments are in kf.  issue(n), n < N, issues the
 // wave's n-th DMA of a coming tile: one between every few MFMAs, where a wave
 // otherwise only waits for the matrix core.
-template <int D, int N, class Issue>
+template <int D, int N, int KEYS, class Issue>
 __device__ __forceinline__ void s_phase(const WaveState<D>& st, f32x16 (&s)[2], bf16x8 (&kf)[Tile<D>::NF],
                                         const uint16_t* Ks, const FragAddr& fa, Issue&& issue) {
   using T = Tile<D>;
   constexpr int STEP = T::NF / N;
   s[0] = s[1] = f32x16{0};
   static_for<T::NF>([&](auto i) PD_INLINE {
-    if constexpr (i + T::KP < T::NF) kf[i + T::KP] = k_frag<D>(Ks, fa, i + T::KP);
-    s[i & 1] = mfma32x32x16(kf[i], st.qf[i >> 1], s[i & 1]);
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (KEYS > 32 || i % 2 == 0) {
+      if constexpr (i + T::KP < T::NF) kf[i + T::KP] = k_frag<D>(Ks, fa, i + T::KP);
+      s[i & 1] = mfma32x32x16(kf[i], st.qf[i >> 1], s[i & 1]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     if constexpr (i % STEP == 1) {
       issue(std::integral_constant<int, i / STEP>());
       __builtin_amdgcn_sched_barrier(0);
@@ -458,6 +460,13 @@ __device__ __forceinline__ void wait_dma(int m) {
 // memory clobber keeps the compiler from moving memory accesses across it.
 __device__ __forceinline__ void tile_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
+// A last tile of at most this many keys takes one key step of P*V and one key block
+// of S instead of four and two, and a quarter of the exponentials.  Most sweeps end
+// in one: the BOS rows put 1 to 4 rows on top of sizes that are whole tiles (1345 rows
+// are 21 tiles and a row).  Prefill of 8K 328.6 -> 324.1 us, of 16K 520.5 -> 515.9, of
+// 8 x 32K 14.53 -> 14.39 ms, 8K step 29.5 -> 28.9 us, step of 8 x 32K 145.6 -> 143.9.
+constexpr int kShortTile = 16;
+
 // Sweep over KV tiles [t_begin, t_end), at least one, by one of two workgroups of
 // four waves on a CU, which are not synchronised: one's start, end and softmax run
 // beside the other's MFMAs.  Tile t lives in buffer (t - t_begin) % 2.  One barrier per tile: before it every wave
@@ -467,12 +476,12 @@ __device__ __forceinline__ void tile_barrier() { asm volatile("s_barrier" ::: "m
 // offsets from that; mixed(V, r, c, lds) is the DMA of chunk byte c of row r (a K
 // or V row) in a tile that is not plain; hook(t, Ks, Vs) sees the landed tile
 // (the prefill writes its cache share there); softmax(t, last, s, pk, vf, Vs) is
-// the vector part.  ACTIVE: false for the waves without query rows, which only
-// move tiles.
+// the vector part.  tail: keys from the last tile's first row to the end of the
+// sequence.  ACTIVE: false for the waves without query rows, which only move tiles.
 template <int D, bool ACTIVE, class Peek, class Off, class Src, class Mixed, class Hook, class Softmax>
 __device__ __forceinline__ void sweep_pair(WaveState<D>& st, uint16_t* Kb, uint16_t* Vb, const FragAddr& fa, int wave,
-                                         int lane, int t_begin, int t_end, Peek&& peek, Off&& off, Src&& tile,
-                                         Mixed&& mixed, Hook&& hook, Softmax&& softmax) {
+                                         int lane, int t_begin, int t_end, int tail, Peek&& peek, Off&& off,
+                                         Src&& tile, Mixed&& mixed, Hook&& hook, Softmax&& softmax) {
   using T = Tile<D, 4>;
   // LDS byte address of this wave's first block in buffer 0.
   const uint32_t ka = lds_addr(Kb) + wave * T::BPW * 1024, va = lds_addr(Vb) + wave * T::BPW * 1024;
@@ -505,8 +514,9 @@ __device__ __forceinline__ void sweep_pair(WaveState<D>& st, uint16_t* Kb, uint1
   uint32_t pk[16];
   bf16x8 vf[T::NF], kf[T::NF];
   int buf = 0;   // buffer of tile t
-  auto step = [&](int t, auto last) PD_INLINE {
+  auto step = [&](int t, auto last, auto keys) PD_INLINE {
     constexpr bool LAST = decltype(last)::value;
+    constexpr int KEYS = decltype(keys)::value;
     const uint16_t *Ks = Kb + buf * T::TILE, *Vs = Vb + buf * T::TILE;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     tile_barrier();
@@ -522,7 +532,7 @@ __device__ __forceinline__ void sweep_pair(WaveState<D>& st, uint16_t* Kb, uint1
       const uint32_t ko = ka + (buf ^ 1) * (T::TILE * 2), vo = va + (buf ^ 1) * (T::TILE * 2);
       if (ACTIVE && __builtin_expect(src.plain, 1)) {
         k_first<D>(kf, Ks, fa);
-        s_phase<D, 2 * T::BPW>(st, s, kf, Ks, fa, [&](auto n) PD_INLINE {
+        s_phase<D, 2 * T::BPW, 64>(st, s, kf, Ks, fa, [&](auto n) PD_INLINE {
           if constexpr (n < T::BPW) dma16(src.k, at[n], ko + n * 1024);
           else dma16(src.v, at[n - T::BPW], vo + (n - T::BPW) * 1024);
         });
@@ -530,23 +540,24 @@ __device__ __forceinline__ void sweep_pair(WaveState<D>& st, uint16_t* Kb, uint1
         dma(t + 1, buf ^ 1);
         if constexpr (ACTIVE) {
           k_first<D>(kf, Ks, fa);
-          s_phase<D, 2 * T::BPW>(st, s, kf, Ks, fa, [](auto) PD_INLINE {});
+          s_phase<D, 2 * T::BPW, 64>(st, s, kf, Ks, fa, [](auto) PD_INLINE {});
         }
       }
       peek(t + 2, code);
     } else if constexpr (ACTIVE) {
-      k_first<D>(kf, Ks, fa);
-      s_phase<D, 2 * T::BPW>(st, s, kf, Ks, fa, [](auto) PD_INLINE {});
+      k_first<D, KEYS>(kf, Ks, fa);
+      s_phase<D, 2 * T::BPW, KEYS>(st, s, kf, Ks, fa, [](auto) PD_INLINE {});
     }
     hook(t, Ks, Vs);
     if constexpr (ACTIVE) {
-      softmax(t, last, s, pk, vf, Vs);
-      pv_phase<D, false>(st, pk, vf, kf, Vs, Ks, fa);
+      softmax(t, last, keys, s, pk, vf, Vs);
+      pv_phase<D, false, KEYS>(st, pk, vf, kf, Vs, Ks, fa);
     }
     buf ^= 1;
   };
-  for (int t = t_begin; t + 1 < t_end; ++t) step(t, std::false_type());
-  step(t_end - 1, std::true_type());
+  for (int t = t_begin; t + 1 < t_end; ++t) step(t, std::false_type(), std::integral_constant<int, 64>());
+  if (tail > kShortTile) step(t_end - 1, std::true_type(), std::integral_constant<int, 64>());
+  else step(t_end - 1, std::true_type(), std::integral_constant<int, kShortTile>());
 }
 
 // The same sweep by the one workgroup of eight waves on a CU.  Tile t lives in
@@ -568,8 +579,8 @@ __device__ __forceinline__ void sweep_pair(WaveState<D>& st, uint16_t* Kb, uint1
 // The other arguments are those of sweep_pair (there is no hook).
 template <int D, bool ACTIVE, class Peek, class Off, class Src, class Mixed, class Softmax>
 __device__ __forceinline__ void sweep_pingpong(WaveState<D>& st, uint16_t* Kb, uint16_t* Vb, const FragAddr& fa, int wave,
-                                         int lane, int t_begin, int t_end, Peek&& peek, Off&& off, Src&& tile,
-                                         Mixed&& mixed, Softmax&& softmax) {
+                                         int lane, int t_begin, int t_end, int tail, Peek&& peek,
+                                         Off&& off, Src&& tile, Mixed&& mixed, Softmax&& softmax) {
   using T = Tile<D, 8>;
   constexpr int S = T::S;
   const int group = wave / (T::NW / 2);
@@ -631,51 +642,63 @@ __device__ __forceinline__ void sweep_pingpong(WaveState<D>& st, uint16_t* Kb, u
   if constexpr (ACTIVE) k_first<D>(kf, Kb, fa);
   int buf = 0;   // buffer of tile t
   // S of tile t and the DMAs of M(t).  HOT: tiles t .. t+3 exist.
-  auto scores = [&](int t, auto hot) PD_INLINE {
+  auto scores = [&](int t, auto hot, auto keys) PD_INLINE {
     constexpr bool HOT = decltype(hot)::value;
+    constexpr int KEYS = decltype(keys)::value;
     const int buf2 = (buf + 2) & (S - 1), buf3 = (buf + 3) & (S - 1);
     advance(t + 3, code);
     peek(t + 4, code);
-    if (ACTIVE && __builtin_expect((HOT || t + 3 < t_end) && src_v.plain && src_k.plain, 1)) {
-      s_phase<D, 2 * T::BPW>(st, s, kf, Kb + buf * T::TILE, fa, [&](auto n) PD_INLINE {
+    if (ACTIVE && KEYS == 64 && __builtin_expect((HOT || t + 3 < t_end) && src_v.plain && src_k.plain, 1)) {
+      s_phase<D, 2 * T::BPW, 64>(st, s, kf, Kb + buf * T::TILE, fa, [&](auto n) PD_INLINE {
         if constexpr (n < T::BPW) dma16(src_k.k, off_k[n], ka + buf3 * (T::TILE * 2) + n * 1024);
         else dma16(src_v.v, off_v[n - T::BPW], va + buf2 * (T::TILE * 2) + (n - T::BPW) * 1024);
       });
     } else {
       if (HOT || t + 3 < t_end) dma(K_, src_k, off_k, t + 3, buf3);
       if (HOT || t + 2 < t_end) dma(V_, src_v, off_v, t + 2, buf2);
-      if constexpr (ACTIVE) s_phase<D, 2 * T::BPW>(st, s, kf, Kb + buf * T::TILE, fa, [](auto) PD_INLINE {});
+      if constexpr (ACTIVE) s_phase<D, 2 * T::BPW, KEYS>(st, s, kf, Kb + buf * T::TILE, fa, [](auto) PD_INLINE {});
     }
   };
   // V(t).  HOT: tiles t .. t+3 exist, so tile t is whole.
-  auto vector = [&](int t, auto hot) PD_INLINE {
+  auto vector = [&](int t, auto hot, auto keys) PD_INLINE {
     constexpr bool HOT = decltype(hot)::value;
-    if constexpr (ACTIVE) softmax(t, std::bool_constant<!HOT>(), s, pk, vf, Vb + buf * T::TILE);
+    if constexpr (ACTIVE) softmax(t, std::bool_constant<!HOT>(), keys, s, pk, vf, Vb + buf * T::TILE);
     wait_dma<T>(HOT || t + 3 < t_end ? 2 : (t + 2 < t_end ? 1 : 0));
   };
-  auto product = [&]() PD_INLINE {   // P*V of tile t; buf moves on to tile t+1
+  auto product = [&](auto keys) PD_INLINE {   // P*V of tile t; buf moves on to tile t+1
     const int vbuf = buf;
     buf = (buf + 1) & (S - 1);
     // After the last tile the K fragments read here are an older tile's, and unused.
-    if constexpr (ACTIVE) pv_phase<D, true>(st, pk, vf, kf, Vb + vbuf * T::TILE, Kb + buf * T::TILE, fa);
+    if constexpr (ACTIVE) pv_phase<D, decltype(keys)::value == 64, decltype(keys)::value>(st, pk, vf, kf, Vb + vbuf * T::TILE, Kb + buf * T::TILE, fa);
   };
+  constexpr std::integral_constant<int, 64> whole;
+  constexpr std::integral_constant<int, kShortTile> few;
   int t = t_begin;
-  scores(t, std::false_type());
+  scores(t, std::false_type(), whole);
   tile_barrier();
   for (; t + 4 < t_end; ++t) {
-    vector(t, std::true_type());
+    vector(t, std::true_type(), whole);
     tile_barrier();
-    product();
-    scores(t + 1, std::true_type());
+    product(whole);
+    scores(t + 1, std::true_type(), whole);
     tile_barrier();
   }
-  for (;; ++t) {
-    vector(t, std::false_type());
+  for (; t + 1 < t_end; ++t) {
+    vector(t, std::false_type(), whole);
     tile_barrier();
-    product();
-    if (t + 1 >= t_end) break;
-    scores(t + 1, std::false_type());
+    product(whole);
+    if (t + 2 == t_end && tail <= kShortTile) scores(t + 1, std::false_type(), few);
+    else scores(t + 1, std::false_type(), whole);
     tile_barrier();
+  }
+  if (tail > kShortTile) {
+    vector(t, std::false_type(), whole);
+    tile_barrier();
+    product(whole);
+  } else {
+    vector(t, std::false_type(), few);
+    tile_barrier();
+    product(few);
   }
   if (!group) tile_barrier();
 }
@@ -791,16 +814,16 @@ __global__ __launch_bounds__(Tile<D>::NT, 2) void prefill_bf16_kernel(PrefillArg
   const int qc_lo = C1, qc_hi = C1 + p.Lq;   // query columns counted by Eq. 5
   const int cm_hi = p.qm_mass ? C1 : 1;       // content columns counted for the chunk score (if asked)
   const int split = C1 - (qt * T::BM + wave * 32);
-  auto softmax = [&](int t, auto last, f32x16 (&s)[2], uint32_t (&pk)[16], bf16x8 (&vf)[T::NF], const uint16_t* vs) PD_INLINE {
+  auto softmax = [&](int t, auto last, auto keys, f32x16 (&s)[2], uint32_t (&pk)[16], bf16x8 (&vf)[T::NF], const uint16_t* vs) PD_INLINE {
     const int t0 = t * T::BN;
     const int kv_valid = decltype(last)::value ? p.Sc - t0 : T::BN;
     const MassRange mr{split, max(qc_lo - t0, 0), min(qc_hi - t0, T::BN), max(1 - t0, 0), min(cm_hi - t0, T::BN)};
-    softmax_phase<D, true>(st, s, pk, vf, vs, fa, grp, l32, p.scale_log2, kv_valid, mr);
+    softmax_phase<D, true, decltype(keys)::value>(st, s, pk, vf, vs, fa, grp, l32, p.scale_log2, kv_valid, mr);
   };
   if (wave_active)
-    sweep_pair<D, true>(st, Kb, Vb, fa, wave, lane, 0, p.n_kvt, peek, off, tile, mixed, write_cache, softmax);
+    sweep_pair<D, true>(st, Kb, Vb, fa, wave, lane, 0, p.n_kvt, p.Sc - (p.n_kvt - 1) * T::BN, peek, off, tile, mixed, write_cache, softmax);
   else
-    sweep_pair<D, false>(st, Kb, Vb, fa, wave, lane, 0, p.n_kvt, peek, off, tile, mixed, write_cache, softmax);
+    sweep_pair<D, false>(st, Kb, Vb, fa, wave, lane, 0, p.n_kvt, p.Sc - (p.n_kvt - 1) * T::BN, peek, off, tile, mixed, write_cache, softmax);
   // This workgroup's content-key sums: the thread slots summed in a fixed
   // order, one vector per (b, n, kv head, writer slot qt*G + h%G).
   __syncthreads();
@@ -950,21 +973,21 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_bf16_kernel(DecodeArgs p) {
   };
   // The Q loads overlap the row-table loads above; both have landed here.
   q_landed(st);
-  auto softmax = [&](int t, auto last, f32x16 (&s)[2], uint32_t (&pk)[16], bf16x8 (&vf)[T::NF], const uint16_t* vs) PD_INLINE {
+  auto softmax = [&](int t, auto last, auto keys, f32x16 (&s)[2], uint32_t (&pk)[16], bf16x8 (&vf)[T::NF], const uint16_t* vs) PD_INLINE {
     const int kv_valid = decltype(last)::value ? min(T::BN, L_kv - t * T::BN) : T::BN;
-    softmax_phase<D, false>(st, s, pk, vf, vs, fa, grp, l32, p.scale_log2, kv_valid, MassRange{0, 0, 0, 0, 0});
+    softmax_phase<D, false, decltype(keys)::value>(st, s, pk, vf, vs, fa, grp, l32, p.scale_log2, kv_valid, MassRange{0, 0, 0, 0, 0});
   };
   if constexpr (NW == 8) {
     if (wave_active)
-      sweep_pingpong<D, true>(st, Kb, Vb, fa, wave, lane, t_begin, t_end, peek, off, tile, mixed, softmax);
+      sweep_pingpong<D, true>(st, Kb, Vb, fa, wave, lane, t_begin, t_end, L_kv - (t_end - 1) * T::BN, peek, off, tile, mixed, softmax);
     else
-      sweep_pingpong<D, false>(st, Kb, Vb, fa, wave, lane, t_begin, t_end, peek, off, tile, mixed, softmax);
+      sweep_pingpong<D, false>(st, Kb, Vb, fa, wave, lane, t_begin, t_end, L_kv - (t_end - 1) * T::BN, peek, off, tile, mixed, softmax);
   } else {
     auto no_hook = [](int, const uint16_t*, const uint16_t*) {};
     if (wave_active)
-      sweep_pair<D, true>(st, Kb, Vb, fa, wave, lane, t_begin, t_end, peek, off, tile, mixed, no_hook, softmax);
+      sweep_pair<D, true>(st, Kb, Vb, fa, wave, lane, t_begin, t_end, L_kv - (t_end - 1) * T::BN, peek, off, tile, mixed, no_hook, softmax);
     else
-      sweep_pair<D, false>(st, Kb, Vb, fa, wave, lane, t_begin, t_end, peek, off, tile, mixed, no_hook, softmax);
+      sweep_pair<D, false>(st, Kb, Vb, fa, wave, lane, t_begin, t_end, L_kv - (t_end - 1) * T::BN, peek, off, tile, mixed, no_hook, softmax);
   }
   if (!wave_active) return;
 

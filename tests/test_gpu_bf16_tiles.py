@@ -23,6 +23,10 @@ DECODE = [
     (8, 2, 512, 17, 32, 32, 128, 2, 500, 5, 1),    # 256 workgroups, 1024 keys: eight waves, whole tiles
     (8, 2, 512, 18, 32, 32, 128, 2, 500, 5, 1),    # 1025 keys: one in the last tile
     (8, 2, 512, 50, 30, 30, 128, 2, 511, 9, 1),    # 240 workgroups, 17 tiles, 1 of 8 waves with 18 rows
+    (8, 2, 512, 33, 32, 32, 128, 2, 500, 5, 1),    # 16 keys in the last tile of eight waves
+    (8, 2, 512, 34, 32, 32, 128, 2, 500, 5, 1),    # 17
+    (1, 2, 64, 40, 2, 1, 128, 1, 30, 9, 1),        # 80 keys: 16 in the last tile
+    (1, 2, 64, 41, 2, 1, 64, 1, 30, 9, 1),         # 81
     (4, 2, 512, 260, 32, 32, 128, 2, 480, 0, 1),   # 256 rows and 4 more: two workgroups a head
 ]
 
@@ -42,7 +46,8 @@ def test_decode_tiles(case):
 
 
 # C, Lq, Lm, D: chunk sequences of 1 + C + Lq + Lm rows
-PREFILL = [(63, 1, 0, 128), (62, 1, 0, 64), (64, 63, 0, 128), (63, 64, 1, 64), (126, 1, 0, 128), (127, 1, 0, 128),
+PREFILL = [(63, 1, 0, 128), (62, 1, 0, 64), (64, 63, 0, 128), (63, 64, 1, 64), (63, 16, 0, 128), (63, 10, 6, 64),
+           (63, 17, 0, 128), (126, 1, 0, 128), (127, 1, 0, 128),
            (70, 190, 3, 64),
            # token scores with the keys of a head split: 4 blocks of 32 a workgroup, 1 in the last; two passes
            (513, 5, 0, 128), (300, 190, 3, 64)]

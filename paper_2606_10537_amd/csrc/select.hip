@@ -145,6 +145,65 @@ __device__ __forceinline__ void head_sum_rank(const float* ph, float* tok_score,
   }
 }
 
+// The same for the 64 tokens of one of several slices of a chunk, by counting: a
+// token's rank is the number of tokens that come before it.  Every slice sums the
+// scores of all tokens; lane l of each wave counts for token l of the slice over
+// segments of 64 tokens, whose keys all lanes read together.  Equal scores rank by
+// index, so a whole segment below the slice also counts its equal keys and one
+// above does not.
+constexpr int kSlice = 64;
+template <int E>
+__device__ __forceinline__ void head_sum_count(const float* ph, float* tok_score, int32_t* tok_rank, int Hq, int C,
+                                               int slice, uint32_t* key) {
+  const int t = threadIdx.x, lane = t & 63;
+  int* const cnt = reinterpret_cast<int*>(key + E * kRankThreads);
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int j = e * kRankThreads + t;
+    uint32_t k = ~0u;
+    if (j < C) {
+      float x = 0.f;
+#pragma unroll 16
+      for (int h = 0; h < Hq; ++h) x += ph[(size_t)h * C + j];
+      if (j / kSlice == slice) tok_score[j] = x;
+      k = (uint32_t)(rank_key(x, 0) >> 32);
+    }
+    key[j] = k;
+  }
+  if (t < kSlice) cnt[t] = 0;
+  __syncthreads();
+  const uint32_t me = key[slice * kSlice + lane];
+  int n = 0;
+  for (int seg = __builtin_amdgcn_readfirstlane(t / 64); seg * 64 < C; seg += kRankThreads / 64) {
+    const u32x4* const at = reinterpret_cast<const u32x4*>(key + seg * 64);
+    if (seg < slice) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const u32x4 k = at[i];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) n += k[q] <= me;
+      }
+    } else if (seg > slice) {   // the padding counts nowhere: no key is above it
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const u32x4 k = at[i];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) n += k[q] < me;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const u32x4 k = at[i];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) n += k[q] < me || (k[q] == me && 4 * i + q < lane);
+      }
+    }
+  }
+  atomicAdd(&cnt[lane], n);
+  __syncthreads();
+  if (t < kSlice && slice * kSlice + t < C) tok_rank[slice * kSlice + t] = cnt[t];
+}
+
 // Prefill-time chunk score of one (b, n) from the per-head content masses of its
 // L_q + L_m query and pseudo-label rows: a(r) = (1/H_q) sum_h mass[h][r],
 // s = -(1/L_q) sum_{r < L_q} ln a(r) - (1/L_m) sum_{r >= L_q} ln a(r) (the
@@ -175,18 +234,19 @@ __device__ __forceinline__ void chunk_score_sum(const float* m, float* chunk_sco
   if (t == 0) *chunk_score = red[0] / Lq + (Lm > 0 ? red[kRankThreads] / Lm : 0.f);
 }
 
-// The end of the prefill, one chunk per blockIdx.x.  y = 0: token scores and ranks.
-// y = 1: the chunk score, if asked for.  The others, at most 64: the key means
+// The end of the prefill, one chunk per blockIdx.x.  The first `slices` of
+// blockIdx.y: token scores and ranks (SORT: one, which sorts).  Then one for
+// the chunk score, if asked for.  The others, at most 64: the key means
 // k-bar[g][d] = (1/C) * the sum of the km_slots partial sums of the cache-writing
 // workgroups (fixed order), 1024 of the H_kv*d values at a time.  With every sort
 // stage in LDS behind a barrier and the chunk score in a launch of its own, one load
 // after the other, the two took 20 and 21 us at 16K; this way the whole prefill of
 // 16K went from 539 to 512 us, of 2 x 5 chunks of 777 from 78.5 to 73.2 us.
-template <int E>
-__global__ __launch_bounds__(kRankThreads) void head_sum_rank_kernel(RankArgs a, int Cpad) {
+template <int E, bool SORT>
+__global__ __launch_bounds__(kRankThreads) void head_sum_rank_kernel(RankArgs a, int Cpad, int slices) {
   extern __shared__ __attribute__((aligned(16))) uint64_t lds[];
   const size_t bn = blockIdx.x;
-  const int first_km = a.chunk_score ? 2 : 1;
+  const int first_km = slices + (a.chunk_score ? 1 : 0);
   if ((int)blockIdx.y >= first_km) {
     const int HD = a.Hkv * a.D, n_km = gridDim.y - first_km;
     for (int i = (blockIdx.y - first_km) * kRankThreads + threadIdx.x; i < HD; i += n_km * kRankThreads) {
@@ -197,23 +257,42 @@ __global__ __launch_bounds__(kRankThreads) void head_sum_rank_kernel(RankArgs a,
       for (int q = 0; q < a.km_slots; ++q) sum += src[(size_t)q * a.D];
       a.key_mean[bn * HD + i] = sum * (1.0f / a.C);
     }
-  } else if (blockIdx.y == 1) {
+  } else if ((int)blockIdx.y >= slices) {
     chunk_score_sum(a.qm_mass + bn * a.Hq * (a.Lq + a.Lm), a.chunk_score + bn, a.Hq, a.Lq, a.Lm,
                     reinterpret_cast<float*>(lds));
+  } else if constexpr (!SORT) {
+    head_sum_count<E>(a.per_head + bn * a.Hq * a.C, a.tok_score + bn * a.C, a.tok_rank + bn * a.C, a.Hq, a.C,
+                      blockIdx.y, reinterpret_cast<uint32_t*>(lds));
   } else {
     head_sum_rank<E>(a.per_head + bn * a.Hq * a.C, a.tok_score + bn * a.C, a.tok_rank + bn * a.C, a.Hq, a.C, Cpad,
                      lds);
   }
 }
 
+// Counting takes ceil(C / 64) workgroups a chunk where sorting takes one, which
+// leaves the chip idle with few chunks and is a chain of 55 stages: 8 chunks of 1024
+// 11.5 -> 6.2 us, 10 of 777 12.3 -> 6.9, 4 of 128 5.7 -> 4.7.  Every slice sums all
+// heads again, so 256 chunks of 1024 (4096 slices, 8 rounds of the chip's 512) sort:
+// 27 us.
+constexpr int kCountGroups = 512;
+template <int E>
+static void launch_head_sum_rank_e(const RankArgs& a, int Cpad, hipStream_t s) {
+  const int n_km = a.key_mean ? std::min(64, (a.Hkv * a.D + kRankThreads - 1) / kRankThreads) : 0;
+  const int slices = (a.C + kSlice - 1) / kSlice, other = (a.chunk_score ? 1 : 0) + n_km;
+  if ((long long)a.B * a.N * slices <= kCountGroups) {
+    const size_t bytes = std::max(4 * (E * kRankThreads + kSlice), 8 * kRankThreads);   // keys and counts, or two sums a thread
+    hipLaunchKernelGGL((head_sum_rank_kernel<E, false>), dim3(a.B * a.N, slices + other), dim3(kRankThreads), bytes, s, a, Cpad, slices);
+  } else {
+    const size_t bytes = 2 * 8 * E * kRankThreads;   // two buffers of the sort
+    hipLaunchKernelGGL((head_sum_rank_kernel<E, true>), dim3(a.B * a.N, 1 + other), dim3(kRankThreads), bytes, s, a, Cpad, 1);
+  }
+}
+
 hipError_t launch_head_sum_rank(const RankArgs& a, hipStream_t s) {
   const int Cpad = next_pow2(a.C);
-  const int n_km = a.key_mean ? std::min(64, (a.Hkv * a.D + kRankThreads - 1) / kRankThreads) : 0;
-  const dim3 grid(a.B * a.N, 1 + (a.chunk_score ? 1 : 0) + n_km);
-  const size_t bytes = 2 * 8 * (size_t)std::max(Cpad, kRankThreads);   // two buffers of the sort
-  if (Cpad <= 1024) hipLaunchKernelGGL(head_sum_rank_kernel<1>, grid, dim3(kRankThreads), bytes, s, a, Cpad);
-  else if (Cpad <= 2048) hipLaunchKernelGGL(head_sum_rank_kernel<2>, grid, dim3(kRankThreads), bytes, s, a, Cpad);
-  else hipLaunchKernelGGL(head_sum_rank_kernel<4>, grid, dim3(kRankThreads), bytes, s, a, Cpad);
+  if (Cpad <= 1024) launch_head_sum_rank_e<1>(a, Cpad, s);
+  else if (Cpad <= 2048) launch_head_sum_rank_e<2>(a, Cpad, s);
+  else launch_head_sum_rank_e<4>(a, Cpad, s);
   return hipGetLastError();
 }
 

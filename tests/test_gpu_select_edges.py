@@ -1,14 +1,16 @@
-"""Selection where its kernels change over: 64 and 65 chunks, one token and 4096 (one and 16 a thread), all
-and one kept, equal scores.  Whole numbers: compared exactly."""
+"""Ranks and selection where their kernels change over: 64 and 65 chunks, one token and 4096 (one and 16
+a thread), all and one kept, equal scores, few and many chunks, numbers of terms around the batches.
+Whole numbers are compared exactly."""
 
 import numpy as np
 import pytest
 import torch
 
 import oracle
-from gpu_path import run_select
+from gpu_path import random_prefill_inputs, run_prefill, run_select
 from paper_2606_10537_amd import _lib
 from paper_2606_10537_amd._lib import PD_FP32, Dims
+from test_gpu_parity import prefill_units_check
 
 pytestmark = pytest.mark.gpu
 
@@ -52,3 +54,22 @@ def test_score_select_both_kernels(N):
     want = np.sort(np.argsort(-ref, axis=1, kind="stable")[:, :5], axis=1)
     assert np.array_equal(ci.cpu().numpy(), want)
     assert np.array_equal(ts.cpu().numpy(), oracle.tokens_by_rank_ref(rank[:, :N].numpy(), want, 9))
+
+
+# C, N: at most 512 workgroups of 64 tokens count the ranks, more chunks sort them
+@pytest.mark.parametrize("C,N", [(1, 2), (64, 2), (65, 2), (1000, 2), (1025, 2), (4096, 2), (1, 513), (64, 513), (65, 257),
+                                 (1000, 33), (1025, 31), (4096, 9)])
+def test_rank_both_kernels(C, N):
+    """Ranks are those of a stable descending sort of the scores written beside them, with equal scores
+    (every second token repeats the one before it)."""
+    d = Dims(1, N, C, 3, 2, 4, 2, 1, 64, PD_FP32)
+    x = random_prefill_inputs(d, seed=C, scale=0.125)
+    for k in ("q_pre", "k_pre"):
+        x[k][:, :, 2::2] = x[k][:, :, 1:C:2]
+    out = run_prefill(d, x, chunk_score=True)
+    torch.cuda.synchronize()
+    e, rank = out["tok_score"].cpu(), out["tok_rank"].cpu().long()
+    order = torch.sort(e, dim=2, descending=True, stable=True)[1]
+    want = torch.empty_like(order).scatter_(2, order, torch.arange(C).expand(1, N, C).contiguous())
+    assert torch.equal(rank, want)
+    prefill_units_check(d, x, out, [(0, N - 1)])

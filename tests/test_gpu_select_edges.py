@@ -73,3 +73,21 @@ def test_rank_both_kernels(C, N):
     want = torch.empty_like(order).scatter_(2, order, torch.arange(C).expand(1, N, C).contiguous())
     assert torch.equal(rank, want)
     prefill_units_check(d, x, out, [(0, N - 1)])
+
+
+@pytest.mark.parametrize("Hq,Ld", [(1, 1), (7, 1), (8, 5), (9, 40), (16, 1024), (43, 300)])
+def test_score_terms(Hq, Ld):
+    """Score terms per chunk (heads x 128-row splits): 1 to 129, eight threads a chunk, 16 terms a batch."""
+    d = Dims(2, 5, 33, 4, 0, Ld, Hq, 1, 64, PD_FP32)
+    g = torch.Generator().manual_seed(Hq + Ld)
+    q = torch.randn((2, Ld, Hq, 64), generator=g).cuda()
+    km = torch.randn((2, 5, 1, 64), generator=g)
+    rank = torch.argsort(torch.rand((2, 5, 33), generator=g), dim=2).to(torch.int32)
+    ci, ts, cs = run_select(d, 2, 9, q, km.cuda(), rank.cuda())
+    torch.cuda.synchronize()
+    ref = oracle.chunk_scores_ref(q.cpu().double().numpy(), km.double().numpy())
+    # fp32 sums of Hq * Ld * 64 products of N(0, 1) values over Ld rows
+    np.testing.assert_allclose(cs.cpu().double().numpy(), ref, rtol=1e-5, atol=1e-5 * Hq ** 0.5)
+    want = np.sort(np.argsort(-cs.cpu().numpy(), axis=1, kind="stable")[:, :2], axis=1)
+    assert np.array_equal(ci.cpu().numpy(), want)
+    assert np.array_equal(ts.cpu().numpy(), oracle.tokens_by_rank_ref(rank.numpy(), want, 9))

@@ -770,8 +770,11 @@ hipError_t launch_gather_joint(const JointArgs& a, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// Split-S merge: O = sum_s 2^(lse_s - M) O_s / sum_s 2^(lse_s - M).
-template <bool BF16>
+// Split-S merge: O = sum_s 2^(lse_s - M) O_s / sum_s 2^(lse_s - M), in ascending shard
+// order.  U > 0: at most U shards, whose LSE and rows are all loaded before the first
+// use: one trip to memory (17 shards of 1024 rows 5.8 -> 4.2 us, 4 shards of 8192 rows
+// 4.8 -> 4.5).  U = 0: any number, first the LSE, then the rows, 8 at a time.
+template <bool BF16, int U>
 __global__ __launch_bounds__(256) void merge_kernel(const float* o_part, const float* lse_part, void* o_dec,
                                                      float* lse_dec, int S, int B, int Hq, int Ld, int D) {
   const int TPR = D / 4;
@@ -780,35 +783,51 @@ __global__ __launch_bounds__(256) void merge_kernel(const float* o_part, const f
   const size_t row = gid / TPR;
   if (row >= rows) return;
   const int c = gid % TPR;
-  // Shards in groups of 8 whose loads are all issued before the first use
-  // (the shard count is a run-time value); summed in ascending shard order.
-  constexpr int U = 8;
-  float M = -INFINITY;
-  for (int s0 = 0; s0 < S; s0 += U) {
-    float l[U];
+  constexpr int V = U > 0 ? U : 8;
+  float l[V];
+  f32x4 v[V];
+  auto load_lse = [&](int s0) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) l[u] = s0 + u < S ? lse_part[(s0 + u) * rows + row] : -INFINITY;
+    for (int u = 0; u < V; ++u) l[u] = lse_part[min(s0 + u, S - 1) * rows + row];
+  };
+  auto load_rows = [&](int s0) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) M = fmaxf(M, l[u]);
-  }
-  float W = 0.f;
+    for (int u = 0; u < V; ++u) v[u] = *reinterpret_cast<const f32x4*>(o_part + (min(s0 + u, S - 1) * rows + row) * D + 4 * c);
+  };
+  float M = -INFINITY, W = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int s0 = 0; s0 < S; s0 += U) {
-    float l[U];
-    f32x4 v[U];
+  auto maximum = [&]() {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool in = s0 + u < S;
-      l[u] = in ? lse_part[(s0 + u) * rows + row] : 0.f;
-      v[u] = in ? *reinterpret_cast<const f32x4*>(o_part + ((s0 + u) * rows + row) * D + 4 * c) : f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int u = 0; u < V; ++u) M = fmaxf(M, l[u]);
+  };
+  auto add = [&](int s0) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < V; ++u) {
       if (s0 + u < S) {
         const float w = fast_exp2(l[u] - M);
         W += w;
         acc += w * v[u];
       }
+    }
+  };
+  if constexpr (U > 0) {
+    load_lse(0);
+    load_rows(0);
+    // Issued here: the compiler would sink each load to its use.
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < V; ++u) asm volatile("" ::"v"(v[u]));
+    maximum();
+    add(0);
+  } else {
+    for (int s0 = 0; s0 < S; s0 += V) {
+      load_lse(s0);
+      maximum();
+    }
+    for (int s0 = 0; s0 < S; s0 += V) {
+      load_lse(s0);
+      load_rows(s0);
+      add(s0);
     }
   }
   const float inv = 1.0f / W;
@@ -831,10 +850,20 @@ hipError_t launch_merge(const float* o_part, const float* lse_part, void* o_dec,
                         int Hq, int Ld, int head_dim, bool bf16, hipStream_t s) {
   const size_t threads = (size_t)B * Hq * Ld * (head_dim / 4);
   const dim3 grid((unsigned)((threads + 255) / 256));
-  if (bf16)
-    hipLaunchKernelGGL(merge_kernel<true>, grid, dim3(256), 0, s, o_part, lse_part, o_dec, lse_dec, S, B, Hq, Ld, head_dim);
-  else
-    hipLaunchKernelGGL(merge_kernel<false>, grid, dim3(256), 0, s, o_part, lse_part, o_dec, lse_dec, S, B, Hq, Ld, head_dim);
+#define PD_MERGE(BF, U) \
+  hipLaunchKernelGGL((merge_kernel<BF, U>), grid, dim3(256), 0, s, o_part, lse_part, o_dec, lse_dec, S, B, Hq, Ld, head_dim)
+#define PD_MERGE_UP_TO(U) \
+  if (S <= U || U == 0) {   \
+    if (bf16) PD_MERGE(true, U); else PD_MERGE(false, U); \
+    return hipGetLastError(); \
+  }
+  PD_MERGE_UP_TO(4)
+  PD_MERGE_UP_TO(8)
+  PD_MERGE_UP_TO(16)
+  PD_MERGE_UP_TO(24)
+  PD_MERGE_UP_TO(0)
+#undef PD_MERGE_UP_TO
+#undef PD_MERGE
   return hipGetLastError();
 }
 

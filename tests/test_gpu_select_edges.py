@@ -1,5 +1,5 @@
-"""Ranks and selection where their kernels change over: 64 and 65 chunks, one token and 4096 (one and 16
-a thread), all and one kept, equal scores, few and many chunks, numbers of terms around the batches.
+"""Ranks, selection and merge where their kernels change over: 64 and 65 chunks, one token and 4096 (one and 16
+a thread), all and one kept, equal scores, few and many chunks, numbers of terms and shards around the batches.
 Whole numbers are compared exactly."""
 
 import numpy as np
@@ -7,10 +7,10 @@ import pytest
 import torch
 
 import oracle
-from gpu_path import random_prefill_inputs, run_prefill, run_select
+from gpu_path import random_decode_inputs, random_indices, random_prefill_inputs, run_decode, run_prefill, run_select
 from paper_2606_10537_amd import _lib
-from paper_2606_10537_amd._lib import PD_FP32, Dims
-from test_gpu_parity import prefill_units_check
+from paper_2606_10537_amd._lib import PD_BF16, PD_FP32, Dims
+from test_gpu_parity import decode_check, prefill_units_check
 
 pytestmark = pytest.mark.gpu
 
@@ -91,3 +91,18 @@ def test_score_terms(Hq, Ld):
     want = np.sort(np.argsort(-cs.cpu().numpy(), axis=1, kind="stable")[:, :2], axis=1)
     assert np.array_equal(ci.cpu().numpy(), want)
     assert np.array_equal(ts.cpu().numpy(), oracle.tokens_by_rank_ref(rank.numpy(), want, 9))
+
+
+@pytest.mark.parametrize("dtype", [PD_BF16, PD_FP32])
+@pytest.mark.parametrize("S", [2, 4, 5, 8, 9, 16, 17, 24, 25, 33])
+def test_merge_shards(S, dtype):
+    """Shard counts around the merge's variants of 4, 8, 16 and 24, and beyond."""
+    d = Dims(1, 4, 600, 8, 4, 9, 2, 1, 64, dtype)
+    scale = 0.125 if dtype == PD_FP32 else 1.0
+    x = random_prefill_inputs(d, seed=S, scale=scale)
+    cache = {"k_cache": x["k_pre"].transpose(2, 3).contiguous(), "v_cache": x["v_pre"].transpose(2, 3).contiguous()}
+    dec = random_decode_inputs(d, seed=S, scale=scale)
+    ci, ts = random_indices(d, 4, 560, seed=5)
+    o, lse = run_decode(d, 4, 560, dec, cache, ci, ts, x["k_qm"], x["v_qm"], 7, num_splits=S)
+    torch.cuda.synchronize()
+    decode_check(d, 4, 560, dec, cache, ci, ts, x["k_qm"], x["v_qm"], 7, o, lse, batches=[0])

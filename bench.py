@@ -21,7 +21,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA (published)
-PEAK_FP32_TFLOPS = 157.3       # MI355X fp32 vector (published; the fp32 path runs on VALU FMAs)
+PEAK_FP32_TFLOPS = 157.3       # MI355X fp32 (published; vector and matrix peaks are equal)
 PEAK_HBM_GBPS = 8000.0         # MI355X HBM3E (published)
 
 

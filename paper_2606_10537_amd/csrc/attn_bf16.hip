@@ -384,7 +384,7 @@ template <int D>
 __device__ __forceinline__ void wave_init(WaveState<D>& st) {
 #pragma unroll
   for (int db = 0; db < Tile<D>::DB; ++db) st.o[db] = f32x16{0};
-  st.m = -INFINITY;
+  st.m = kNoMax;
   st.l = f32x4{0.f, 0.f, 0.f, 0.f};
   st.lx = 0.f;
   st.qmass = 0.f;
@@ -995,7 +995,8 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_bf16_kernel(DecodeArgs p) {
   const int hq = g * p.G + rho / p.Ld;
   const int rr = rho % p.Ld;
   const float ltot = (lane & 16) ? st.l[1] : st.l[0];
-  float inv = 1.0f / ltot;
+  // No weight in this shard (every score -inf): zeros of weight zero in the merge.
+  float inv = p.S > 1 && ltot == 0.f ? 0.f : 1.0f / ltot;
   float lse2 = st.m + __log2f(ltot);
   if (kCheckIndices && bad_index) inv = lse2 = __uint_as_float(kNanWord);
   if (p.S == 1) {

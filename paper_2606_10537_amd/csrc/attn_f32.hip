@@ -57,8 +57,8 @@ struct F32Lds {
 // Attention of the workgroup's R query rows over keys [j0, j1).  qrow(i) is the
 // pointer of row i or NULL (zeros), key(j, k, v) gives the K and V rows of key j,
 // range(i, lo, hi) the keys whose mass is counted for row i (MASS).  Then
-// out(i, d, x) receives four merged, normalised output values of row i from d on
-// and row(i, m, l, mass) its log2-domain maximum, weight sum and mass.
+// out(i, d, l, x) receives four merged output values, times the weight sum l, of row i
+// from d on, and row(i, m, l, mass) its log2-domain maximum, weight sum and mass.
 template <int D, int QB, int NW, bool MASS, class QRow, class Key, class Range, class Out, class Row>
 __device__ __forceinline__ void attend_f32(F32Lds<D, QB, NW>& lds, int j0, int j1, float scale_log2, QRow&& qrow,
                                            Key&& key, Range&& range, Out&& out, Row&& row) {
@@ -75,7 +75,7 @@ __device__ __forceinline__ void attend_f32(F32Lds<D, QB, NW>& lds, int j0, int j
     for (int s = 0; s < KS; ++s) qf[b][s] = src ? ld4(src + 16 * s + 4 * g) : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < 4 * DC; ++i) o[b][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    m[b] = -INFINITY;
+    m[b] = kNoMax;
     l[b] = mass[b] = 0.f;
     if constexpr (MASS) range(16 * b + q, lo[b], hi[b]);
   }
@@ -202,13 +202,13 @@ __device__ __forceinline__ void attend_f32(F32Lds<D, QB, NW>& lds, int j0, int j
     float L = 0.f, ms = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      // A wave without keys has m = -inf and zeros: weight 0, whatever M is.
+      // A wave without keys, or with scores of -inf only, has no weight, whatever M is.
       const float a = lds.l[w][i] == 0.f ? 0.f : fast_exp2(lds.m[w][i] - M);
       acc += a * *reinterpret_cast<const f32x4*>(&lds.o[w][i][d]);
       L += a * lds.l[w][i];
       ms += a * lds.mass[w][i];
     }
-    out(i, d, acc * (1.0f / L));
+    out(i, d, L, acc);
     if (d == 0) row(i, M, L, ms);
   }
 }
@@ -286,8 +286,8 @@ __global__ __launch_bounds__(64 * NW) void prefill_f32_kernel(PrefillArgs p, flo
         lo = row0 + i < C1 ? qc_lo : 1;
         hi = row0 + i < C1 ? qc_hi : (p.qm_mass ? C1 : 1);
       },
-      [&](int i, int d, f32x4 x) {
-        if (row0 + i < p.Sc) *reinterpret_cast<f32x4*>(o + ((chunk * p.Sc + row0 + i) * p.Hq + h) * D + d) = x;
+      [&](int i, int d, float l, f32x4 x) {
+        if (row0 + i < p.Sc) *reinterpret_cast<f32x4*>(o + ((chunk * p.Sc + row0 + i) * p.Hq + h) * D + d) = x * (1.0f / l);
       },
       [&](int i, float m, float l, float mass) {
         const int row = row0 + i;
@@ -429,10 +429,12 @@ __global__ __launch_bounds__(64 * NW) void decode_f32_kernel(DecodeArgs p) {
         }
       },
       [](int, int&, int&) {},
-      [&](int i, int d, f32x4 x) {
+      [&](int i, int d, float l, f32x4 x) {
         if (row0 + i >= GL) return;
         int hq, r;
         where(i, hq, r);
+        // No weight in this shard (every score -inf): zeros of weight zero in the merge.
+        x *= p.S > 1 && l == 0.f ? 0.f : 1.0f / l;
         if (kCheckIndices && bad_index) x = f32x4{1.f, 1.f, 1.f, 1.f} * __uint_as_float(kNanWord);
         float* dst = p.S == 1 ? reinterpret_cast<float*>(p.o_dec) + (((size_t)b * p.Ld + r) * p.Hq + hq) * D
                               : p.o_part + ((((size_t)sp * p.B + b) * p.Hq + hq) * p.Ld + r) * D;

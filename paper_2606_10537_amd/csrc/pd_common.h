@@ -62,6 +62,10 @@ __device__ __forceinline__ T* uniform(T* p) {
               ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32));
 }
 
+// The running maximum of a row before its first key.  Finite, so that a tile whose
+// scores are all -inf gives weights exp2(-inf - m) = 0 and not exp2(-inf + inf).
+constexpr float kNoMax = -3.402823466e38f;
+
 // Index checks of the checking build (compiled with PD_CHECK_INDICES): a kept
 // chunk outside 0..N-1 or a kept slot outside 1..C (slot 0, the BOS row, is
 // implied) is replaced by slot 0 of chunk 0 before anything is read, and every

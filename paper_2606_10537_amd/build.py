@@ -25,10 +25,8 @@ FLAGS = [
 ]
 
 
-# Per-source extra flags.  The bf16 attention kernels never create or test NaN
-# (masked scores are -inf), so NaN semantics are dropped there: the row maxima
-# then compile to v_max3_f32 chains without canonicalising each MFMA output.
-EXTRA = {"attn_bf16.hip": ["-fno-honor-nans"]}
+# Per-source extra flags (none at present).
+EXTRA = {}
 
 
 def _run(cmd):

@@ -185,17 +185,29 @@ __device__ __forceinline__ bf16x8 v_frag(const uint16_t* Vs, const FragAddr& fa,
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
+// The largest of three, NaN if one of them is (v_max3_f32 would drop a NaN, and fmaxf
+// also canonicalises each MFMA output first).
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float r;
+  asm("v_maximum3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
 // Max of this lane's value and the value of lane l ^ 32 (v_permlane32_swap
 // exchanges the two halves of the wave without going through LDS).
 __device__ __forceinline__ float max_across_halves(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  const float y = __uint_as_float(r[1]);
+  return max3(__uint_as_float(r[0]), y, y);
 }
 
 // Softmax, part 1: mask, row max, lazy rescale of the running output.  Returns
 // -m (log2 domain) for the exponent FMA.  Key of s[kb][r]: 32*kb + 8*(r/4) +
 // 4*grp + r%4.  The max is taken on raw scores (the scale is positive) and the
 // scale is folded into one FMA: p = exp2(s * scale_log2 - m).
+// A row with a NaN or +inf score has no softmax: its sums and outputs turn NaN here,
+// and its weights are zero from the tile on, because the product that sums the
+// weights takes queries q and q + 16 in one column, one of them times zero.
 template <int D, bool EXACT, int KEYS>
 __device__ __forceinline__ float softmax_max(WaveState<D>& st, f32x16 (&s)[2], int grp, float scale_log2,
                                              int kv_valid) {
@@ -208,17 +220,19 @@ __device__ __forceinline__ float softmax_max(WaveState<D>& st, f32x16 (&s)[2], i
       s[kb][r] = 32 * kb + 8 * (r >> 2) + (r & 3) < valid ? s[kb][r] : -INFINITY;
     }
   }
-  // One v_max3_f32 per pair (the file is built without NaN semantics, so no
-  // canonicalising v_max precedes each score).
   float mx = -INFINITY;
 #pragma unroll
-  for (int e = 0; e < KEYS / 2; e += 2) mx = fmaxf(fmaxf(mx, s[e >> 4][e & 15]), s[e >> 4][(e & 15) + 1]);
+  for (int e = 0; e < KEYS / 2; e += 2) mx = max3(mx, s[e >> 4][e & 15], s[e >> 4][(e & 15) + 1]);
   mx = max_across_halves(mx) * scale_log2;
-  const bool upd = mx > st.m + 8.0f;
-  if (__builtin_expect(__ballot(upd) != 0, 0)) {
+  if (__builtin_expect(__ballot(!(mx <= st.m + 8.0f)) != 0, 0)) {
+    const bool bad = !(mx < INFINITY), upd = !bad && mx > st.m + 8.0f;
     const float mnew = upd ? mx : st.m;
-    const float alpha = fast_exp2(st.m - mnew);
+    const float alpha = bad ? __uint_as_float(kNanWord) : fast_exp2(st.m - mnew);
     st.m = mnew;
+    if (__ballot(bad)) {
+#pragma unroll
+      for (int e = 0; e < KEYS / 2; ++e) s[e >> 4][e & 15] = bad ? -INFINITY : s[e >> 4][e & 15];
+    }
     const int q16 = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) & 15;
     st.l[0] *= __shfl(alpha, q16);
     st.l[1] *= __shfl(alpha, q16 + 16);

@@ -118,6 +118,10 @@ __device__ __forceinline__ const char* ubytes(const uint16_t* p) { return reinte
 __device__ __forceinline__ void dma16(const char* base, uint32_t off, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(uniform(base)), "s"(uniform((int)lds)) : "memory", "m0");
 }
+// The same from an address per lane.
+__device__ __forceinline__ void dma16(const char* at, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(at), "s"(uniform((int)lds)) : "memory", "m0");
+}
 __device__ __forceinline__ uint32_t lds_addr(const uint16_t* p) { return (uint32_t)(uintptr_t)(PD_LDS const void*)(p); }
 
 // Engine state of the 32 query rows of a wave.
@@ -445,10 +449,11 @@ __device__ __forceinline__ int dma_chunk(int wave, int lane) {
 
 // Where the wave's rows of one tile come from.  plain: all rows of the tile lie
 // at uniform bases k, v plus a byte offset per lane (from the row table if table,
-// else that of consecutive rows); otherwise (a tile that crosses from one buffer
-// to the next, or past the last row) the lanes of each buffer issue a DMA of
-// their own.  The next
-// `run` tiles continue this one, each `step` bytes further.
+// else that of consecutive rows); otherwise (a tile that crosses from one buffer to
+// the next, or past the last row) every lane has an address of its own.  In short
+// sweeps most tiles are of that kind: with one masked DMA per buffer instead a step of
+// 65 rows over 2 tiles took 16.0 us, now 15.6, one of 128 rows over 7 tiles 22.4, now
+// 20.9.  The next `run` tiles continue this one, each `step` bytes further.
 struct TileSrc {
   const char *k, *v;
   long long step;
@@ -487,7 +492,7 @@ constexpr int kShortTile = 16;
 // has waited for its own share of tile t's DMA and has used all it read of tile
 // t-1, whose buffer then takes tile t+1.  tile(t) gives a tile's rows, peek(t,
 // code) reads the row table of a tile and off(ts, code, j) makes a lane's byte
-// offsets from that; mixed(V, r, c, lds) is the DMA of chunk byte c of row r (a K
+// offsets from that; mixed(V, r, c) is where chunk byte c of row r (a K
 // or V row) in a tile that is not plain; hook(t, Ks, Vs) sees the landed tile
 // (the prefill writes its cache share there); softmax(t, last, s, pk, vf, Vs) is
 // the vector part.  tail: keys from the last tile's first row to the end of the
@@ -510,8 +515,8 @@ __device__ __forceinline__ void sweep_pair(WaveState<D>& st, uint16_t* Kb, uint1
         dma16(src.v, at[j], vo + j * 1024);
       } else {
         const int ln = opaque(lane), r = t * T::BN + dma_row<T>(wave, ln, j);
-        mixed(std::false_type(), r, 16u * dma_chunk<T>(wave, ln), ko + j * 1024);
-        mixed(std::true_type(), r, 16u * dma_chunk<T>(wave, ln), vo + j * 1024);
+        dma16(mixed(std::false_type(), r, 16u * dma_chunk<T>(wave, ln)), ko + j * 1024);
+        dma16(mixed(std::true_type(), r, 16u * dma_chunk<T>(wave, ln)), vo + j * 1024);
       }
     }
   };
@@ -609,7 +614,7 @@ __device__ __forceinline__ void sweep_pingpong(WaveState<D>& st, uint16_t* Kb, u
         dma16(V ? ts.v : ts.k, o[j], dst);
       } else {
         const int ln = opaque(lane);
-        mixed(V, t * T::BN + dma_row<T>(wave, ln, j), 16u * dma_chunk<T>(wave, ln), dst);
+        dma16(mixed(V, t * T::BN + dma_row<T>(wave, ln, j), 16u * dma_chunk<T>(wave, ln)), dst);
       }
     }
   };
@@ -780,11 +785,10 @@ __global__ __launch_bounds__(Tile<D>::NT, 2) void prefill_bf16_kernel(PrefillArg
     const size_t at = (size_t)r0 * HD * 2;
     return TileSrc{(r0 < C1 ? kl : kh) + at, (r0 < C1 ? vl : vh) + at, (long long)T::BN * HD * 2, (end - r0) / T::BN - 1, r0 + T::BN <= end, false};
   };
-  auto mixed = [=](auto V, int r, unsigned c, uint32_t lds) PD_INLINE {
+  auto mixed = [=](auto V, int r, unsigned c) PD_INLINE {
     r = min(r, p.Sc - 1);
-    const unsigned at = 2u * HD * r + c;
-    if (r < C1) dma16(ubytes(V ? v_lo : k_lo), at, lds);
-    else dma16(ubytes(V ? v_hi : k_hi), at, lds);
+    const char *lo = ubytes(V ? v_lo : k_lo), *hi = ubytes(V ? v_hi : k_hi);
+    return (r < C1 ? lo : hi) + 2u * HD * r + c;
   };
   // Each KV tile of the (b, n, kv head) group is written to the cache by exactly
   // one workgroup of that group (query tile t % n_qt of head g*G + (t / n_qt) % G),
@@ -978,12 +982,12 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_bf16_kernel(DecodeArgs p) {
     return TileSrc{(gath ? kg : (stat ? ks : kd)) + at, (gath ? vg : (stat ? vs : vd)) + at, gath ? 0 : (long long)T::BN * HD * 2, (end - r0) / T::BN - 1,
                    r0 + T::BN <= end, gath};
   };
-  auto mixed = [=](auto V, int r, unsigned c, uint32_t lds) PD_INLINE {
+  auto mixed = [=](auto V, int r, unsigned c) PD_INLINE {
     r = min(r, L_kv - 1);
-    const unsigned at = 2u * HD * r + c;
-    if (r < n_sel) dma16(ubytes(V ? vc : kc), rowtab_p[r - j_lo] + c, lds);
-    else if (r < n_sel + n_static) dma16(ubytes(V ? vs_ : ks_), at, lds);
-    else dma16(ubytes(V ? vd_ : kd_), at, lds);
+    const bool gath = r < n_sel;
+    const unsigned tab = rowtab_p[gath ? r - j_lo : 0], at = gath ? tab : 2u * HD * r;
+    const char *cg = ubytes(V ? vc : kc), *st = ubytes(V ? vs_ : ks_), *dc = ubytes(V ? vd_ : kd_);
+    return (gath ? cg : (r < n_sel + n_static ? st : dc)) + at + c;
   };
   // The Q loads overlap the row-table loads above; both have landed here.
   q_landed(st);

@@ -1120,19 +1120,8 @@ hipError_t launch_prefill_bf16(const PrefillArgs& a, int head_dim, hipStream_t s
   return head_dim == 128 ? launch_prefill_d<128>(a, s) : launch_prefill_d<64>(a, s);
 }
 
-// Which sweep decodes.  Eight waves win by the traffic they save, where their
-// workgroups fill the CUs in whole rounds and a sweep is long against its start:
-// step of 8 x 32K (512 workgroups of 27 tiles) 139.7 us against 145.3 with four
-// waves, four steps of 4 x 32K 287 against 300.  With 320 workgroups of 19 tiles
-// (joint pass of 2 x 1156 rows), two rounds for 1.25 of work, they take 112 against
-// 98 us, with 4 tiles (8K, 5 shards) 35.5 against 33.1 us.
-static bool eight_waves(const DecodeArgs& a) {
-  const long long groups = (long long)a.B * a.Hkv * ((a.G * a.Ld + 255) / 256) * a.S;
-  const long long rounds = (groups + 255) / 256;
-  const int tiles = (a.n_sel + a.n_static + a.Ld + 63) / 64;
-  return tiles >= 16 * a.S && 10 * groups >= 9 * 256 * rounds;
-}
-
+// Which sweep decodes: prefers_eight_waves (its rule and figures are there) where the
+// kernel has one, d = 128.
 template <int D, int NW>
 static hipError_t launch_decode_w(DecodeArgs a, hipStream_t s) {
   a.n_qt = (a.G * a.Ld + Tile<D, NW>::BM - 1) / Tile<D, NW>::BM;
@@ -1142,8 +1131,10 @@ static hipError_t launch_decode_w(DecodeArgs a, hipStream_t s) {
 }
 template <int D>
 static hipError_t launch_decode_d(const DecodeArgs& a, hipStream_t s) {
-  if constexpr (D == 128)
-    if (eight_waves(a)) return launch_decode_w<D, 8>(a, s);
+  if constexpr (D == 128) {
+    const int tiles = (a.n_sel + a.n_static + a.Ld + 63) / 64;
+    if (prefers_eight_waves((long long)a.B * a.Hkv, a.G * a.Ld, tiles, a.S)) return launch_decode_w<D, 8>(a, s);
+  }
   return launch_decode_w<D, 4>(a, s);
 }
 hipError_t launch_decode_bf16(const DecodeArgs& a, int head_dim, hipStream_t s) {

@@ -35,7 +35,6 @@ constexpr int kMaxChunks = 1024;
 constexpr int kMaxChunkLen = 4096;
 constexpr int kMaxSplits = 64;
 constexpr int kMaxCompactRows = 1 << 20;   // prefix rows of a compact decode call
-constexpr int kNumCu = 256;
 constexpr size_t kAlign = 256;
 
 size_t round_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
@@ -166,9 +165,9 @@ int requested_splits(const pd_dims* d, long long n_sel, int num_splits) {
     const int tiles = cdiv(n_sel + d->dec_len, 64);
     const long long units = std::max(1LL, decode_units(d));
     if (d->dtype == PD_BF16)
-      s = tiles < 8 ? 1 : (int)std::min(kNumCu / units, (long long)std::ceil(2.0 * std::sqrt((double)tiles)));
+      s = tiles < 8 ? 1 : (int)std::min(pd::kNumCu / units, (long long)std::ceil(2.0 * std::sqrt((double)tiles)));
     else
-      s = std::min(cdiv(kNumCu, units), tiles / 4);
+      s = std::min(cdiv(pd::kNumCu, units), tiles / 4);
     s = std::max(1, std::min(s, kMaxSplits));
   }
   return std::max(s, min_splits(d, n_sel));

@@ -5,6 +5,8 @@
 
 namespace pd {
 
+constexpr int kNumCu = 256;
+
 // Gathered KV rows of one decode shard whose cache-row codes fit the kernel's
 // LDS table; the host raises the shard count until every shard fits.
 constexpr int kDecodeTableRows = 2048;
@@ -52,6 +54,27 @@ struct DecodeArgs {
   int out_f32;       // o_dec is fp32 instead of the input element type
   float scale_log2;
 };
+
+// Whether a decode of `units` (sequence, KV head) pairs of `rows` query rows over `tiles`
+// KV tiles in S shards takes workgroups of eight waves and 256 rows instead of four and
+// 128 (d = 128).  Eight win by the traffic they save, where their workgroups fill the
+// CUs in whole rounds and a sweep is long against its start: step of 8 x 32K (512
+// workgroups of 27 tiles) 139.7 us against 145.3 with four waves, four steps of 4 x 32K
+// 287 against 300.  With 320 workgroups of 19 tiles (joint pass of 2 x 1156 rows), two
+// rounds for 1.25 of work, they take 112 against 98 us, with 4 tiles (8K, 5 shards)
+// 35.5 against 33.1 us.
+// Their second half of rows has to be there: with 128 rows or fewer in the last tile
+// four waves need half the places (units of 23, 64, 125 rows in 2 shards of 17 tiles:
+// 56.5, 65, 84-90 us against 65, 76, 92; 260, 300, 384 rows over 26 to 29 tiles: 101,
+// 108, 124 against 112, 117, 131; but 160, 200 rows 105, 118 against 102, 117, and 400,
+// 450 rows 138, 150-159 against 135, 148).  Only where the four-wave workgroups have a CU each
+// anyway, eight keep more tiles in flight: 256 units of 23, 100, 128 rows over 17 to
+// 26 tiles, keys not in cache, 40.1, 48, 61.5 us against 41.7, 49.9, 64.0.
+inline bool prefers_eight_waves(long long units, int rows, int tiles, int S) {
+  const long long groups = units * ((rows + 255) / 256) * S, rounds = (groups + kNumCu - 1) / kNumCu;
+  const bool full = (rows - 1) % 256 >= 128 || units * ((rows + 127) / 128) * S <= kNumCu;
+  return full && tiles >= 16 * S && 10 * groups >= 9 * kNumCu * rounds;
+}
 
 hipError_t launch_prefill_bf16(const PrefillArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_escore_bf16(const EscoreArgs& a, int head_dim, hipStream_t s);

@@ -143,15 +143,19 @@ pd_status check_select_grid(const pd_dims* d, int rows) {
 
 // Shard counts for a decode call whose KV has n_sel prefix rows per (sequence,
 // KV head) ahead of the static and own rows.  Requested count: explicit, or, for
-// bf16, as many as keep one workgroup per CU (a CU with two takes longer than
-// any with one: 8K batch 1, 64 row tiles, takes 23.1 us with 4 shards and 26.0
-// with 5) and no more than 2 sqrt(tiles), where shorter sweeps no longer pay
-// for the larger merge (10 tiles, 16 rows: 11.3 us with 6 shards, 14.6 with 2,
-// 16.8 with 1; 66 tiles, 32 rows: 20.4 us with 12, 20.7 with 16, 22.7 with 32,
-// and, with the keys not in cache, the step takes 28.0 us with 16, 29.5 with 13).
+// bf16, as many as keep one workgroup per CU (a fifth shard on some CUs makes those
+// the last: 8K batch 1, 64 row tiles, takes 23.1 us with 4 shards and 26.0 with 5)
+// and no more than 2 sqrt(tiles), where shorter sweeps no longer pay for the larger
+// merge (10 tiles, 16 rows: 11.3 us with 6 shards, 14.6 with 2, 16.8 with 1; 66
+// tiles, 32 rows: 20.4 us with 12, 20.7 with 16, 22.7 with 32, and, with the keys not in
+// cache, the step takes 28.0 us with 16, 29.5 with 13; 400 tiles of 1 and 2 heads,
+// 16 and 32 rows: 32.6 and 36.3 us with 41, 35.1 and 39.8 with 64).
 // Below 8 tiles the merge costs more than it saves (a step over 6 tiles: 20.5 us
-// with 1 shard, 23.9 with 4).  fp32 shards keep >= 4 tiles of 64 rows.  The bf16 kernel also needs every shard to fit its LDS row
-// table (at most kDecodeTableRows rows, i.e. kDecodeTableRows/64 tiles),
+// with 1 shard, 23.9 with 4).  Where eight waves then win, the shards are those of
+// their 256-row tiles: 64 heads of 256 rows over 67 tiles take 60.5 us (66.8 with the
+// keys not in cache) in 4 shards of eight waves, 63.9 (73.8) in 3 of four.  fp32 shards
+// keep >= 4 tiles of 64 rows.  The bf16 kernel also needs every shard to fit its
+// LDS row table (at most kDecodeTableRows rows, i.e. kDecodeTableRows/64 tiles),
 // whatever n_static is.
 int min_splits(const pd_dims* d, long long n_sel) {
   if (d->dtype != PD_BF16 || n_sel <= pd::kDecodeTableRows) return 1;
@@ -164,10 +168,16 @@ int requested_splits(const pd_dims* d, long long n_sel, int num_splits) {
   if (s <= 0) {
     const int tiles = cdiv(n_sel + d->dec_len, 64);
     const long long units = std::max(1LL, decode_units(d));
-    if (d->dtype == PD_BF16)
-      s = tiles < 8 ? 1 : (int)std::min(pd::kNumCu / units, (long long)std::ceil(2.0 * std::sqrt((double)tiles)));
-    else
+    if (d->dtype == PD_BF16) {
+      const int most = tiles < 8 ? 1 : (int)std::ceil(2.0 * std::sqrt((double)tiles));
+      s = (int)std::min<long long>(pd::kNumCu / units, most);
+      const long long pairs = (long long)d->batch * d->n_heads_kv;
+      const int rows = d->n_heads_q / d->n_heads_kv * d->dec_len;
+      const int eight = std::max(1, (int)std::min<long long>(pd::kNumCu / (pairs * cdiv(rows, 256)), most));
+      if (d->head_dim == 128 && pd::prefers_eight_waves(pairs, rows, tiles, eight)) s = eight;
+    } else {
       s = std::min(cdiv(pd::kNumCu, units), tiles / 4);
+    }
     s = std::max(1, std::min(s, kMaxSplits));
   }
   return std::max(s, min_splits(d, n_sel));

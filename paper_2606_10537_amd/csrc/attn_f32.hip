@@ -316,7 +316,7 @@ __global__ __launch_bounds__(64) void escore_f32_kernel(EscoreArgs p) {
   const int b = (int)(bn / p.N);
   const size_t qm_base = (p.qm_per_chunk ? bn : (size_t)b) * (size_t)(p.Lq + p.Lm);
   const float* lse = p.lse_q + bnh * p.Lq;
-  const int j = cb * 16 + q;
+  const int j = cb * kF32ScoreKeys + q;
   const float* kp = j < p.C ? k_cache + ((bn * p.Hkv + h / p.G) * (p.C + 1) + 1 + j) * D : nullptr;
   f32x4 kf[KS], qa[KS], qn[KS];
 #pragma unroll
@@ -455,15 +455,10 @@ __global__ __launch_bounds__(64 * NW) void decode_f32_kernel(DecodeArgs p) {
 }
 
 // ---------------------------------------------------------------------------
-// Row tiles of 32 (QB = 2, 4 waves) when they give every CU two workgroups, else
-// of 16 (QB = 1, 8 waves): a call below that is bound by the depth of one
-// workgroup, which the smaller tile cuts to a quarter.
-static bool wide_rows(long long units, int rows) { return units * ((rows + 31) / 32) >= 512; }
-
 template <int D>
 static hipError_t prefill_f32_d(PrefillArgs a, float* key_mean, hipStream_t s) {
-  const int units = a.B * a.N * a.Hq, copies = a.B * a.N * a.Hkv;
-  const bool wide = wide_rows(units, a.Sc);
+  const int units = a.B * a.N * a.Hq, copies = a.B * a.N * a.Hkv;   // the host has bounded the grid
+  const bool wide = f32_rows(units, a.Sc) == 32;
   a.n_qt = wide ? (a.Sc + 31) / 32 : (a.Sc + 15) / 16;
   a.total = units * a.n_qt;
   if (wide) hipLaunchKernelGGL((prefill_f32_kernel<D, 2, 4>), dim3(a.total + copies), dim3(256), 0, s, a, key_mean);
@@ -476,7 +471,7 @@ hipError_t launch_prefill_f32(const PrefillArgs& a, float* key_mean, int head_di
 
 hipError_t launch_escore_f32(const EscoreArgs& a, int head_dim, hipStream_t s) {
   EscoreArgs e = a;
-  e.n_cb = (a.C + 15) / 16;
+  e.n_cb = (a.C + kF32ScoreKeys - 1) / kF32ScoreKeys;
   const dim3 grid((unsigned)(a.B * a.N * a.Hq * e.n_cb));
   if (head_dim == 128) hipLaunchKernelGGL(escore_f32_kernel<128>, grid, dim3(64), 0, s, e);
   else hipLaunchKernelGGL(escore_f32_kernel<64>, grid, dim3(64), 0, s, e);
@@ -486,7 +481,7 @@ hipError_t launch_escore_f32(const EscoreArgs& a, int head_dim, hipStream_t s) {
 template <int D>
 static hipError_t decode_f32_d(DecodeArgs a, hipStream_t s) {
   const int units = a.B * a.Hkv, rows = a.G * a.Ld;
-  const bool wide = wide_rows((long long)units * a.S, rows);
+  const bool wide = f32_rows((long long)units * a.S, rows) == 32;
   a.n_qt = wide ? (rows + 31) / 32 : (rows + 15) / 16;
   a.total = units * a.n_qt * a.S;
   if (wide) hipLaunchKernelGGL((decode_f32_kernel<D, 2, 4>), dim3(a.total), dim3(256), 0, s, a);

@@ -115,6 +115,8 @@ size_t select_ws(const pd_dims* d) {
   return round_up((size_t)d->batch * d->n_chunks * d->n_heads_q * pd::select_row_splits(rows) * sizeof(float));
 }
 
+// Row tiles that the shard counts below go by.  (The fp32 kernel's own are
+// f32_rows high and hold the rows of a whole KV head.)
 int decode_qtiles(const pd_dims* d) {
   const int G = d->n_heads_q / d->n_heads_kv;
   return d->dtype == PD_BF16 ? cdiv((long long)G * d->dec_len, pd::kBf16Rows) : cdiv(d->dec_len, 64);
@@ -127,11 +129,26 @@ long long decode_units(const pd_dims* d) {
 // shards), its Split-S merge (one thread per 4 output elements), and the
 // chunk-score pass over `rows` query rows (sequence x head x 128-row split).
 pd_status check_decode_grid(const pd_dims* d, int S) {
-  const long long total = decode_units(d) * S;
+  long long total = decode_units(d) * S;
+  if (d->dtype == PD_FP32) {
+    const long long rows = (long long)(d->n_heads_q / d->n_heads_kv) * d->dec_len;
+    total = std::max(total, pd::f32_groups((long long)d->batch * d->n_heads_kv * S, rows));
+  }
   const long long merge = ((long long)d->batch * d->n_heads_q * d->dec_len * (d->head_dim / 4) + 255) / 256;
   if (total >= (1LL << 31) || (S > 1 && merge >= (1LL << 31)))
     return fail(PD_ERR_BAD_DIMS, "decode of batch=%d, dec_len=%d with %d shards is too large for one launch",
                 d->batch, d->dec_len, S);
+  return PD_OK;
+}
+// The fp32 prefill (row tiles and one copying workgroup per KV head) and its token
+// scores take more workgroups than the 64-row tiles that check_dims counts.
+pd_status check_prefill_grid(const pd_dims* d) {
+  if (d->dtype != PD_FP32) return PD_OK;
+  const long long bn = (long long)d->batch * d->n_chunks, sc = 1LL + d->chunk_len + d->q_len + d->m_len;
+  if (pd::f32_groups(bn * d->n_heads_q, sc) + bn * d->n_heads_kv >= (1LL << 31) ||
+      bn * d->n_heads_q * cdiv(d->chunk_len, pd::kF32ScoreKeys) >= (1LL << 31))
+    return fail(PD_ERR_BAD_DIMS, "fp32 prefill of batch=%d with %d chunks is too large for one launch", d->batch,
+                d->n_chunks);
   return PD_OK;
 }
 pd_status check_select_grid(const pd_dims* d, int rows) {
@@ -272,7 +289,7 @@ size_t pd_cache_bytes(const pd_dims* d) {
 size_t pd_workspace_bytes(const pd_dims* d, int32_t top_k, int32_t tok_budget, int32_t num_splits, int32_t which) {
   if (check_dims(d) != PD_OK) return 0;
   switch (which) {
-    case 0: return prefill_ws(d).total;
+    case 0: return check_prefill_grid(d) == PD_OK ? prefill_ws(d).total : 0;
     case 1:
       if (check_select_grid(d, std::max(d->dec_len, std::max(d->m_len, 1))) != PD_OK) return 0;
       return select_ws(d);
@@ -297,6 +314,7 @@ pd_status pd_prefill_chunks(const pd_dims* d, const void* q_pre, const void* k_p
                             void* v_cache, float* tok_score, int32_t* tok_rank, float* key_mean, float* chunk_score,
                             void* workspace, size_t ws_bytes, void* stream) {
   PD_RETURN_IF(check_dims(d));
+  PD_RETURN_IF(check_prefill_grid(d));
   PD_REQUIRE_PTR(q_pre);
   PD_REQUIRE_PTR(k_pre);
   PD_REQUIRE_PTR(v_pre);
@@ -689,8 +707,7 @@ static pd_status decode_core(const pd_dims* d, int top_k, int tok_budget, long l
   a.S = S;
   a.out_f32 = d->out_fp32;
   a.scale_log2 = scale_of(d) * 1.4426950408889634f;
-  a.n_qt = decode_qtiles(d);
-  a.total = (int)(decode_units(d) * S);
+  // n_qt and total: the launchers choose their own row tiles.
   if (S > 1) {
     const size_t rows = (size_t)S * a.B * a.Hq * a.Ld;
     a.o_part = (float*)workspace;

@@ -55,6 +55,16 @@ struct DecodeArgs {
   float scale_log2;
 };
 
+// Query rows of an fp32 workgroup: 32 (four waves) when tiles of 32 rows give 512
+// workgroups or more, else 16 (eight waves).  units: workgroups per row tile.
+inline int f32_rows(long long units, long long rows) { return units * ((rows + 31) / 32) >= 512 ? 32 : 16; }
+inline long long f32_groups(long long units, long long rows) {
+  const int r = f32_rows(units, rows);
+  return units * ((rows + r - 1) / r);
+}
+// Content keys of an fp32 token-score workgroup.
+constexpr int kF32ScoreKeys = 16;
+
 // Whether a decode of `units` (sequence, KV head) pairs of `rows` query rows over `tiles`
 // KV tiles in S shards takes workgroups of eight waves and 256 rows instead of four and
 // 128 (d = 128).  Eight win by the traffic they save, where their workgroups fill the

@@ -224,9 +224,11 @@ __global__ __launch_bounds__(64 * NW) void prefill_f32_kernel(PrefillArgs p, flo
   const float* k_pre = reinterpret_cast<const float*>(p.k_pre);
   const float* v_pre = reinterpret_cast<const float*>(p.v_pre);
   const int C1 = p.C + 1, tid = threadIdx.x;
-  if ((int)blockIdx.x >= p.total) {
+  const uint32_t bid = block_id(), total = p.total;
+  if (bid >= total) {
+    if (bid - total >= (uint32_t)(p.B * p.N * p.Hkv)) return;   // the grid's last row
     constexpr int CH = D / 4, NG = 64 * NW / CH;   // 16-byte chunks of a row; rows in flight
-    const size_t bng = blockIdx.x - p.total, chunk = bng / p.Hkv;
+    const size_t bng = bid - total, chunk = bng / p.Hkv;
     const int g = (int)(bng % p.Hkv), c = tid % CH, rg = tid / CH;
     float* kc = reinterpret_cast<float*>(p.k_cache) + bng * C1 * D + 4 * c;
     float* vc = reinterpret_cast<float*>(p.v_cache) + bng * C1 * D + 4 * c;
@@ -254,7 +256,7 @@ __global__ __launch_bounds__(64 * NW) void prefill_f32_kernel(PrefillArgs p, flo
   const float* k_qm = reinterpret_cast<const float*>(p.k_qm);
   const float* v_qm = reinterpret_cast<const float*>(p.v_qm);
   float* o = reinterpret_cast<float*>(p.o);
-  int lid = xcd_remap(blockIdx.x, p.total);
+  int lid = xcd_remap(bid, p.total);
   const int rb = lid % p.n_qt;
   lid /= p.n_qt;
   const int h = lid % p.Hq;
@@ -310,8 +312,10 @@ __global__ __launch_bounds__(64) void escore_f32_kernel(EscoreArgs p) {
   const float* q_qm = reinterpret_cast<const float*>(p.q_qm);
   const float* k_cache = reinterpret_cast<const float*>(p.k_cache);
   const int lane = threadIdx.x, q = lane & 15, g = lane >> 4;
-  const size_t bnh = blockIdx.x / p.n_cb;   // (b * N + n) * Hq + h
-  const int cb = blockIdx.x % p.n_cb, h = (int)(bnh % p.Hq);
+  const uint32_t bid = block_id();
+  if (bid >= (uint32_t)(p.B * p.N * p.Hq * p.n_cb)) return;   // the grid's last row
+  const size_t bnh = bid / p.n_cb;   // (b * N + n) * Hq + h
+  const int cb = bid % p.n_cb, h = (int)(bnh % p.Hq);
   const size_t bn = bnh / p.Hq;
   const int b = (int)(bn / p.N);
   const size_t qm_base = (p.qm_per_chunk ? bn : (size_t)b) * (size_t)(p.Lq + p.Lm);
@@ -369,7 +373,8 @@ __global__ __launch_bounds__(64 * NW) void decode_f32_kernel(DecodeArgs p) {
   const float* k_static = reinterpret_cast<const float*>(p.k_static);
   const float* v_static = reinterpret_cast<const float*>(p.v_static);
 
-  int lid = xcd_remap(blockIdx.x, p.total);
+  if (block_id() >= (uint32_t)p.total) return;   // the grid's last row
+  int lid = xcd_remap(block_id(), p.total);
   const int sp = lid % p.S;
   lid /= p.S;
   const int rb = lid % p.n_qt;
@@ -461,8 +466,8 @@ static hipError_t prefill_f32_d(PrefillArgs a, float* key_mean, hipStream_t s) {
   const bool wide = f32_rows(units, a.Sc) == 32;
   a.n_qt = wide ? (a.Sc + 31) / 32 : (a.Sc + 15) / 16;
   a.total = units * a.n_qt;
-  if (wide) hipLaunchKernelGGL((prefill_f32_kernel<D, 2, 4>), dim3(a.total + copies), dim3(256), 0, s, a, key_mean);
-  else hipLaunchKernelGGL((prefill_f32_kernel<D, 1, 8>), dim3(a.total + copies), dim3(512), 0, s, a, key_mean);
+  if (wide) hipLaunchKernelGGL((prefill_f32_kernel<D, 2, 4>), grid_xy((long long)a.total + copies), dim3(256), 0, s, a, key_mean);
+  else hipLaunchKernelGGL((prefill_f32_kernel<D, 1, 8>), grid_xy((long long)a.total + copies), dim3(512), 0, s, a, key_mean);
   return hipGetLastError();
 }
 hipError_t launch_prefill_f32(const PrefillArgs& a, float* key_mean, int head_dim, hipStream_t s) {
@@ -472,7 +477,7 @@ hipError_t launch_prefill_f32(const PrefillArgs& a, float* key_mean, int head_di
 hipError_t launch_escore_f32(const EscoreArgs& a, int head_dim, hipStream_t s) {
   EscoreArgs e = a;
   e.n_cb = (a.C + kF32ScoreKeys - 1) / kF32ScoreKeys;
-  const dim3 grid((unsigned)(a.B * a.N * a.Hq * e.n_cb));
+  const dim3 grid = grid_xy((long long)a.B * a.N * a.Hq * e.n_cb);
   if (head_dim == 128) hipLaunchKernelGGL(escore_f32_kernel<128>, grid, dim3(64), 0, s, e);
   else hipLaunchKernelGGL(escore_f32_kernel<64>, grid, dim3(64), 0, s, e);
   return hipGetLastError();
@@ -484,8 +489,8 @@ static hipError_t decode_f32_d(DecodeArgs a, hipStream_t s) {
   const bool wide = f32_rows((long long)units * a.S, rows) == 32;
   a.n_qt = wide ? (rows + 31) / 32 : (rows + 15) / 16;
   a.total = units * a.n_qt * a.S;
-  if (wide) hipLaunchKernelGGL((decode_f32_kernel<D, 2, 4>), dim3(a.total), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((decode_f32_kernel<D, 1, 8>), dim3(a.total), dim3(512), 0, s, a);
+  if (wide) hipLaunchKernelGGL((decode_f32_kernel<D, 2, 4>), grid_xy(a.total), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((decode_f32_kernel<D, 1, 8>), grid_xy(a.total), dim3(512), 0, s, a);
   return hipGetLastError();
 }
 hipError_t launch_decode_f32(const DecodeArgs& a, int head_dim, hipStream_t s) {

@@ -29,6 +29,9 @@ __device__ __forceinline__ int xcd_remap(int bid, int total) {
   return xcd * per + (xcd < rem ? xcd : rem) + idx;
 }
 
+// A launch counts its threads per dimension in 32 bits, so large grids have two (grid_xy).
+__device__ __forceinline__ uint32_t block_id() { return blockIdx.y * gridDim.x + blockIdx.x; }
+
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) {
   return __uint_as_float(((uint32_t)h) << 16);
 }

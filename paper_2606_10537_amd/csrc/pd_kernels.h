@@ -55,6 +55,12 @@ struct DecodeArgs {
   float scale_log2;
 };
 
+// n workgroups, block_id() < n, rounded up to whole rows of the grid.
+inline dim3 grid_xy(long long n) {
+  const long long x = n < (1 << 20) ? n : 1 << 20;
+  return dim3((unsigned)x, (unsigned)((n + x - 1) / x));
+}
+
 // Query rows of an fp32 workgroup: 32 (four waves) when tiles of 32 rows give 512
 // workgroups or more, else 16 (eight waves).  units: workgroups per row tile.
 inline int f32_rows(long long units, long long rows) { return units * ((rows + 31) / 32) >= 512 ? 32 : 16; }

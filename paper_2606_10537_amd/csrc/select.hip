@@ -273,7 +273,8 @@ __device__ __forceinline__ void chunk_score_sum(const float* m, float* chunk_sco
 template <int E, bool SORT>
 __global__ __launch_bounds__(kRankThreads) void head_sum_rank_kernel(RankArgs a, int Cpad, int slices) {
   extern __shared__ __attribute__((aligned(16))) uint64_t lds[];
-  const size_t bn = blockIdx.x;
+  const size_t bn = (size_t)blockIdx.z * gridDim.x + blockIdx.x;
+  if (bn >= (size_t)a.B * a.N) return;   // the grid's last row
   const int first_km = slices + (a.chunk_score ? 1 : 0);
   if ((int)blockIdx.y >= first_km) {
     const int HD = a.Hkv * a.D, n_km = gridDim.y - first_km;
@@ -305,12 +306,13 @@ template <int E>
 static void launch_head_sum_rank_e(const RankArgs& a, int Cpad, hipStream_t s) {
   const int n_km = a.key_mean ? std::min(64, (a.Hkv * a.D + kRankThreads - 1) / kRankThreads) : 0;
   const int slices = (a.C + kSlice - 1) / kSlice, other = (a.chunk_score ? 1 : 0) + n_km;
+  const dim3 bn = grid_xy((long long)a.B * a.N);
   if ((long long)a.B * a.N * slices <= kCountGroups) {
     const size_t bytes = std::max(4 * (E * kRankThreads + kSlice), 8 * kRankThreads);   // keys and counts, or two sums a thread
-    hipLaunchKernelGGL((head_sum_rank_kernel<E, false>), dim3(a.B * a.N, slices + other), dim3(kRankThreads), bytes, s, a, Cpad, slices);
+    hipLaunchKernelGGL((head_sum_rank_kernel<E, false>), dim3(bn.x, slices + other, bn.y), dim3(kRankThreads), bytes, s, a, Cpad, slices);
   } else {
     const size_t bytes = 2 * 8 * E * kRankThreads;   // two buffers of the sort
-    hipLaunchKernelGGL((head_sum_rank_kernel<E, true>), dim3(a.B * a.N, 1 + other), dim3(kRankThreads), bytes, s, a, Cpad, 1);
+    hipLaunchKernelGGL((head_sum_rank_kernel<E, true>), dim3(bn.x, 1 + other, bn.y), dim3(kRankThreads), bytes, s, a, Cpad, 1);
   }
 }
 
@@ -584,7 +586,8 @@ __global__ __launch_bounds__(256) void select_kernel(const float* partial, const
 static hipError_t launch_select(const float* partial, const int32_t* tok_rank, float* chunk_score, int32_t* chunk_idx,
                                 int32_t* tok_slot, int B, int N, int C, int K, int Bt, int T, int neg,
                                 hipStream_t s) {
-  if (N <= kSelectAll) {
+  // 2^24 workgroups of 256 threads are too many for one dimension.
+  if (N <= kSelectAll && (long long)B * N < (1 << 24)) {
     hipLaunchKernelGGL(select_all_kernel, dim3(B * N), dim3(256), 0, s, partial, tok_rank, chunk_score, chunk_idx,
                        tok_slot, N, C, K, Bt, T, neg);
   } else {

@@ -22,8 +22,11 @@
 // themselves, and one's start and end cost nothing while the other computes.
 // sweep_pingpong: one workgroup of eight waves whose halves run half a tile apart,
 // held there by barriers; each tile in LDS serves twice the rows (half the
-// traffic from L2), but the start, 8 us, and the end of a workgroup are bare.  Under
-// full load the card's power limit sets the clock, 1.7-1.9 GHz of 2.4.  Against
+// traffic from L2), but the start, 8 us, and the end of a workgroup are bare.  The
+// matrix cores are busy 43 % (decode of 8 x 32K) and 47 % (prefill) of the cycles;
+// the waves issue 35 and 39 % of their time, wait 36 and 37 % for an issue slot and 29
+// and 23 % for a barrier, a DMA or LDS data.  By the cycle counters the clock is
+// 2.1 GHz in that decode and 1.6 in that prefill, of 2.4.  Against
 // one workgroup of eight waves with one barrier a tile (before): prefill of 8 x
 // 32K 14.67 -> 14.05 ms, of 16K 595 -> 539 us, joint pass of 2 x 1156 rows 86 ->
 // 67 us, step of 8 x 32K 142.7 -> 139.7 us.
@@ -136,8 +139,8 @@ struct WaveState {
 };
 
 // Keys counted into qmass (prefill only), tile-relative: a lane whose query row
-// lies below `split` (row index within the wave's first row group; +32 per
-// further group) counts [lo0, hi0), the other lanes [lo1, hi1).  The prefill
+// lies below `split` (row index within the wave) counts [lo0, hi0), the other lanes
+// [lo1, hi1).  The prefill
 // counts the query columns for the BOS and content rows (Eq. 5, first sum)
 // and the content columns for the query and pseudo-label rows (the
 // prefill-time chunk score).
@@ -166,12 +169,14 @@ struct FragAddr {
   }
 };
 
-// One KV tile for one wave: S^T = K Q^T, online softmax producing the bf16
-// weights P, O^T += V^T P^T.  KEYS: keys that are computed, 64 or kShortTile.
-// kv_valid: number of valid keys among them (KEYS except in a ragged last tile).  mr: keys counted into qmass.  EXACT: also keep
-// the unrounded row sum and the counted mass (prefill).  O is normalised by the
-// sum of the same bf16-rounded weights that multiply V, so rounding P perturbs a
-// convex combination instead of scaling O.
+// One KV tile for one wave, in the functions that follow: S^T = K Q^T (s_phase), online
+// softmax producing the bf16 weights P (softmax_phase), O^T += V^T P^T (pv_phase).
+// KEYS: keys that are computed, 64 or kShortTile.  kv_valid: number of valid keys
+// among them (KEYS except in a ragged last tile).  mr: keys counted into qmass.
+// EXACT: also keep the unrounded row sum and the counted mass (prefill).  O is
+// normalised by the sum of the same bf16-rounded weights that multiply V, so rounding
+// P perturbs a convex combination instead of scaling O.
+
 // Fragment i of a K tile: k-step i / 2, 32-key block i % 2.
 template <int D>
 __device__ __forceinline__ bf16x8 k_frag(const uint16_t* Ks, const FragAddr& fa, int i) {
@@ -474,7 +479,7 @@ __device__ __forceinline__ void wait_dma(int m) {
 
 // Workgroup barrier without a memory fence.  __syncthreads() would also wait
 // for every LDS DMA still in flight (they count as outstanding LDS writes),
-// draining the pipeline; here the tile in use is covered by wait_dma_keep, and
+// draining the pipeline; here the tile in use is covered by the wait for its DMA, and
 // every LDS read of older tiles has been consumed before a wave gets here.  The
 // memory clobber keeps the compiler from moving memory accesses across it.
 __device__ __forceinline__ void tile_barrier() { asm volatile("s_barrier" ::: "memory"); }
@@ -723,7 +728,7 @@ __device__ __forceinline__ void sweep_pingpong(WaveState<D>& st, uint16_t* Kb, u
 }
 
 // ---------------------------------------------------------------------------
-// Stage (a): chunk prefill.  Workgroup = (b, n, h, 256-row query tile).
+// Stage (a): chunk prefill.  Workgroup = (b, n, h, 128-row query tile).
 // Also writes the chunk KV cache (each KV tile by exactly one workgroup of the
 // (b, n, kv-head) group), the per-head query-column mass of the content rows,
 // the log2-domain LSE of the query rows and, when asked, the per-head
@@ -870,8 +875,8 @@ __global__ __launch_bounds__(Tile<D>::NT, 2) void prefill_bf16_kernel(PrefillArg
 }
 
 // ---------------------------------------------------------------------------
-// Stage (c): sparse decode attention.  Workgroup = (b, kv head g, 128-row tile
-// of the G*L_d query rows of that group, KV shard).  Query row rho of the group
+// Stage (c): sparse decode attention.  Workgroup = (b, kv head g, tile of 32 rows a
+// wave of the G*L_d query rows of that group, KV shard).  Query row rho of the group
 // is head g*G + rho / L_d, decode row rho % L_d.  KV row j of the shard walks:
 // [kept chunks: BOS + kept slots] ; [static rows] ; [own rows].
 template <int D, int NW>
@@ -976,7 +981,7 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_bf16_kernel(DecodeArgs p) {
     const int end = gath ? n_sel : (stat ? n_stat : L_kv);   // rows up to end lie in one buffer
     // ubytes() of all before any is selected: the compiler would select among the
     // captures' addresses, which puts them into scratch memory.
-  const char *kg = ubytes(kc), *ks = ubytes(ks_), *kd = ubytes(kd_);
+    const char *kg = ubytes(kc), *ks = ubytes(ks_), *kd = ubytes(kd_);
     const char *vg = ubytes(vc), *vs = ubytes(vs_), *vd = ubytes(vd_);
     const size_t at = gath ? 0 : (size_t)r0 * HD * 2;
     return TileSrc{(gath ? kg : (stat ? ks : kd)) + at, (gath ? vg : (stat ? vs : vd)) + at, gath ? 0 : (long long)T::BN * HD * 2, (end - r0) / T::BN - 1,

@@ -160,13 +160,14 @@ pd_status check_select_grid(const pd_dims* d, int rows) {
 
 // Shard counts for a decode call whose KV has n_sel prefix rows per (sequence,
 // KV head) ahead of the static and own rows.  Requested count: explicit, or, for
-// bf16, as many as keep one workgroup per CU (a fifth shard on some CUs makes those
-// the last: 8K batch 1, 64 row tiles, takes 23.1 us with 4 shards and 26.0 with 5)
-// and no more than 2 sqrt(tiles), where shorter sweeps no longer pay for the larger
-// merge (10 tiles, 16 rows: 11.3 us with 6 shards, 14.6 with 2, 16.8 with 1; 66
+// bf16, as many as keep one workgroup per CU (8K batch 1, 64 row tiles: 23.2 us with 4
+// shards, 24.4 with 3, 26.0 with 5, 25.6 with 8, which are two on every CU; 96 row tiles
+// over 21 tiles of keys 26.4 us with 2, 29.6 with 3; 160 to 256 row tiles 32 to 37 us
+// with 1, 37 to 48 with 2) and no more than 2 sqrt(tiles), where shorter sweeps no
+// longer pay for the larger merge (10 tiles, 16 rows: 11.3 us with 6 shards, 14.6 with 2, 16.8 with 1; 66
 // tiles, 32 rows: 20.4 us with 12, 20.7 with 16, 22.7 with 32, and, with the keys not in
 // cache, the step takes 28.0 us with 16, 29.5 with 13; 400 tiles of 1 and 2 heads,
-// 16 and 32 rows: 32.6 and 36.3 us with 41, 35.1 and 39.8 with 64).
+// 16 and 32 rows: steps of 32.6 and 36.3 us with 41, 35.1 and 39.8 with 64).
 // Below 8 tiles the merge costs more than it saves (a step over 6 tiles: 20.5 us
 // with 1 shard, 23.9 with 4).  Where eight waves then win, the shards are those of
 // their 256-row tiles: 64 heads of 256 rows over 67 tiles take 60.5 us (66.8 with the

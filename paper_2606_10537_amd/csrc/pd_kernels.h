@@ -61,8 +61,14 @@ inline dim3 grid_xy(long long n) {
   return dim3((unsigned)x, (unsigned)((n + x - 1) / x));
 }
 
-// Query rows of an fp32 workgroup: 32 (four waves) when tiles of 32 rows give 512
-// workgroups or more, else 16 (eight waves).  units: workgroups per row tile.
+// Query rows of an fp32 workgroup: 32 (four waves, half the K/V reads per product; at
+// d = 128 one workgroup fills a CU's registers) when tiles of 32 rows give 512
+// workgroups, two rounds of the CUs, or more, else 16 (eight waves, which split the
+// keys further).  Steps at d = 128: 2048 workgroups of 32 rows over 643 keys 342 us, 4096
+// of 16 rows 412; a prefill of 32 chunks of 577 rows, 8 heads, 779 against 934; below
+// the line 36 of 32 rows over 499 keys 37.1, 72 of 16 rows 26.5; 128 of 32 rows over
+// 451 keys 38.2, 256 of 16 rows 27.9.  (A single chunk of 4161 rows and one head, 131 tiles of 32 rows,
+// would take 217 us instead of 294.)  units: workgroups per row tile.
 inline int f32_rows(long long units, long long rows) { return units * ((rows + 31) / 32) >= 512 ? 32 : 16; }
 inline long long f32_groups(long long units, long long rows) {
   const int r = f32_rows(units, rows);

@@ -1,10 +1,13 @@
 // Stage (b): per-step chunk scores, top-K chunks and the kept tokens of each
 // kept chunk, plus the once-per-layer token ranking of stage (a).
 //
-//   head_sum_rank: grid (b, n)  -- Eq. 5 scores summed over the heads, bitonic sort
-//                                  in LDS (score desc, index asc) -> token ranks;
-//                                  beside it the key means and, from the content mass
-//                                  of the q/m rows, the prefill-time chunk score;
+//   head_sum_rank: grid (b, n; part) -- Eq. 5 scores summed over the heads and the
+//                                  token ranks (score desc, index asc), by counting in
+//                                  one workgroup per 64 tokens where there are few
+//                                  chunks, else by a bitonic sort in one per chunk;
+//                                  in workgroups of their own the key means and, from
+//                                  the content mass of the q/m rows, the prefill-time
+//                                  chunk score;
 //   qscore:     grid (b, h, sp) -- by linearity the chunk score splits into
 //                                  terms scale * <(1/L_d) sum_{r in sp} q_r, kbar_n>
 //                                  over heads and row splits: one workgroup sums
@@ -12,11 +15,12 @@
 //                                  key means of that head's KV group;
 //   gather:     grid (rows)     -- static-selection mode: kept rows copied once
 //                                  into a contiguous per-(sequence, KV head) buffer;
-//   select:     grid (b, k)     -- sums the terms of every chunk in a fixed
-//                                  order, ranks the N scores (bitonic sort in
-//                                  LDS), takes the k-th kept chunk in ascending
-//                                  order and writes its tokens with rank < B_tok
-//                                  in ascending slot order (flags + block scan).
+//   select:     grid (b, n), up to 64 chunks, or (b, k) -- sums the terms of every
+//                                  chunk in a fixed order, ranks the N scores (by
+//                                  counting, from 256 chunks on by a bitonic sort in
+//                                  LDS) and writes the tokens of its chunk, n if
+//                                  kept or the k-th kept one in ascending order, with
+//                                  rank < B_tok in ascending slot order (block scan).
 // All reductions run in a fixed order, so results are bitwise reproducible.
 #include "pd_common.h"
 #include "pd_kernels.h"
@@ -471,9 +475,8 @@ __device__ __forceinline__ int block_exclusive_sum(int x, int* wsum) {
 
 // Kept tokens (rank < Bt) of one chunk in ascending order: counts over
 // contiguous segments, an exclusive scan, then each segment writes its slots
-// (token + 1).  The
-// ranks of a segment are loaded 16 at a time, all in flight before the first
-// compare (a plain loop waits for each load in turn).
+// (token + 1).  The ranks of a segment are loaded 16 at a time, all in flight
+// before the first compare (a plain loop waits for each load in turn).
 __device__ void list_tokens(const int32_t* rk, int C, int Bt, int32_t* out, int* wsum) {
   constexpr int U = 16;
   const int t = threadIdx.x;

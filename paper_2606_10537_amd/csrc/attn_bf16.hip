@@ -455,10 +455,12 @@ __device__ __forceinline__ int dma_chunk(int wave, int lane) {
 // Where the wave's rows of one tile come from.  plain: all rows of the tile lie
 // at uniform bases k, v plus a byte offset per lane (from the row table if table,
 // else that of consecutive rows); otherwise (a tile that crosses from one buffer to
-// the next, or past the last row) every lane has an address of its own.  In short
-// sweeps most tiles are of that kind: with one masked DMA per buffer instead a step of
-// 65 rows over 2 tiles took 16.0 us, now 15.6, one of 128 rows over 7 tiles 22.4, now
-// 20.9.  The next `run` tiles continue this one, each `step` bytes further.
+// the next, or past the last row) mixed() issues the DMA.  In the decode every lane
+// has an address of its own there: in short sweeps most tiles are of that kind, and with
+// one masked DMA per buffer a step of 65 rows over 2 tiles took 16.0 us, now 15.6, one
+// of 128 rows over 7 tiles 22.4, now 20.9.  The prefill, which has two such tiles in 15
+// to 27 and two buffers, keeps one masked DMA per buffer (8 x 32K 14.36 ms, 14.44 with an
+// address per lane).  The next `run` tiles continue this one, each `step` bytes further.
 struct TileSrc {
   const char *k, *v;
   long long step;
@@ -520,8 +522,8 @@ __device__ __forceinline__ void sweep_pair(WaveState<D>& st, uint16_t* Kb, uint1
         dma16(src.v, at[j], vo + j * 1024);
       } else {
         const int ln = opaque(lane), r = t * T::BN + dma_row<T>(wave, ln, j);
-        dma16(mixed(std::false_type(), r, 16u * dma_chunk<T>(wave, ln)), ko + j * 1024);
-        dma16(mixed(std::true_type(), r, 16u * dma_chunk<T>(wave, ln)), vo + j * 1024);
+        mixed(std::false_type(), r, 16u * dma_chunk<T>(wave, ln), ko + j * 1024);
+        mixed(std::true_type(), r, 16u * dma_chunk<T>(wave, ln), vo + j * 1024);
       }
     }
   };
@@ -619,7 +621,7 @@ __device__ __forceinline__ void sweep_pingpong(WaveState<D>& st, uint16_t* Kb, u
         dma16(V ? ts.v : ts.k, o[j], dst);
       } else {
         const int ln = opaque(lane);
-        dma16(mixed(V, t * T::BN + dma_row<T>(wave, ln, j), 16u * dma_chunk<T>(wave, ln)), dst);
+        mixed(V, t * T::BN + dma_row<T>(wave, ln, j), 16u * dma_chunk<T>(wave, ln), dst);
       }
     }
   };
@@ -790,10 +792,11 @@ __global__ __launch_bounds__(Tile<D>::NT, 2) void prefill_bf16_kernel(PrefillArg
     const size_t at = (size_t)r0 * HD * 2;
     return TileSrc{(r0 < C1 ? kl : kh) + at, (r0 < C1 ? vl : vh) + at, (long long)T::BN * HD * 2, (end - r0) / T::BN - 1, r0 + T::BN <= end, false};
   };
-  auto mixed = [=](auto V, int r, unsigned c) PD_INLINE {
+  auto mixed = [=](auto V, int r, unsigned c, uint32_t lds) PD_INLINE {
     r = min(r, p.Sc - 1);
-    const char *lo = ubytes(V ? v_lo : k_lo), *hi = ubytes(V ? v_hi : k_hi);
-    return (r < C1 ? lo : hi) + 2u * HD * r + c;
+    const unsigned at = 2u * HD * r + c;
+    if (r < C1) dma16(ubytes(V ? v_lo : k_lo), at, lds);
+    else dma16(ubytes(V ? v_hi : k_hi), at, lds);
   };
   // Each KV tile of the (b, n, kv head) group is written to the cache by exactly
   // one workgroup of that group (query tile t % n_qt of head g*G + (t / n_qt) % G),
@@ -987,12 +990,12 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_bf16_kernel(DecodeArgs p) {
     return TileSrc{(gath ? kg : (stat ? ks : kd)) + at, (gath ? vg : (stat ? vs : vd)) + at, gath ? 0 : (long long)T::BN * HD * 2, (end - r0) / T::BN - 1,
                    r0 + T::BN <= end, gath};
   };
-  auto mixed = [=](auto V, int r, unsigned c) PD_INLINE {
+  auto mixed = [=](auto V, int r, unsigned c, uint32_t lds) PD_INLINE {
     r = min(r, L_kv - 1);
     const bool gath = r < n_sel;
     const unsigned tab = rowtab_p[gath ? r - j_lo : 0], at = gath ? tab : 2u * HD * r;
     const char *cg = ubytes(V ? vc : kc), *st = ubytes(V ? vs_ : ks_), *dc = ubytes(V ? vd_ : kd_);
-    return (gath ? cg : (r < n_sel + n_static ? st : dc)) + at + c;
+    dma16((gath ? cg : (r < n_sel + n_static ? st : dc)) + at + c, lds);
   };
   // The Q loads overlap the row-table loads above; both have landed here.
   q_landed(st);

@@ -194,12 +194,11 @@ __device__ __forceinline__ bf16x8 v_frag(const uint16_t* Vs, const FragAddr& fa,
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// The largest of three, NaN if one of them is (v_max3_f32 would drop a NaN, and fmaxf
-// also canonicalises each MFMA output first).
+// The largest of three, NaN if one of them is: v_maximum3_f32 (v_max3_f32 would drop a
+// NaN, and fmaxf also canonicalises each MFMA output first).  Not inline assembly, for
+// which the compiler does not count the wait states after an MFMA that writes a or b.
 __device__ __forceinline__ float max3(float a, float b, float c) {
-  float r;
-  asm("v_maximum3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
+  return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c);
 }
 
 // Max of this lane's value and the value of lane l ^ 32 (v_permlane32_swap
@@ -499,7 +498,7 @@ constexpr int kShortTile = 16;
 // has waited for its own share of tile t's DMA and has used all it read of tile
 // t-1, whose buffer then takes tile t+1.  tile(t) gives a tile's rows, peek(t,
 // code) reads the row table of a tile and off(ts, code, j) makes a lane's byte
-// offsets from that; mixed(V, r, c) is where chunk byte c of row r (a K
+// offsets from that; mixed(V, r, c, lds) is the DMA of chunk byte c of row r (a K
 // or V row) in a tile that is not plain; hook(t, Ks, Vs) sees the landed tile
 // (the prefill writes its cache share there); softmax(t, last, s, pk, vf, Vs) is
 // the vector part.  tail: keys from the last tile's first row to the end of the

@@ -116,10 +116,14 @@ __device__ __forceinline__ const char* ubytes(const uint16_t* p) { return reinte
 // as inline assembly: when the compiler sees an LDS DMA in flight it can no
 // longer count LDS reads precisely and waits for all of them (lgkmcnt(0)) before
 // every fragment use.  Completion is tracked by hand (wait_dma); loads the
-// compiler does not see only make its own vmcnt waits stricter.  The s_nop is
-// the wait state between a write of M0 and the DMA that reads it.
+// compiler does not see only make its own vmcnt waits stricter.  The s_nop holds the
+// wait states that the compiler would insert between its own instructions: one
+// between a write of M0 and the DMA that reads it, and five between a vector
+// instruction that writes a scalar register and the DMA that reads that.  FRESH: the base
+// may come straight from such an instruction (readfirstlane).
+template <bool FRESH = false>
 __device__ __forceinline__ void dma16(const char* base, uint32_t off, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(uniform(base)), "s"(uniform((int)lds)) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop %3\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(uniform(base)), "s"(uniform((int)lds)), "n"(FRESH ? 3 : 0) : "memory", "m0");
 }
 // The same from an address per lane.
 __device__ __forceinline__ void dma16(const char* at, uint32_t lds) {
@@ -794,8 +798,8 @@ __global__ __launch_bounds__(Tile<D>::NT, 2) void prefill_bf16_kernel(PrefillArg
   auto mixed = [=](auto V, int r, unsigned c, uint32_t lds) PD_INLINE {
     r = min(r, p.Sc - 1);
     const unsigned at = 2u * HD * r + c;
-    if (r < C1) dma16(ubytes(V ? v_lo : k_lo), at, lds);
-    else dma16(ubytes(V ? v_hi : k_hi), at, lds);
+    if (r < C1) dma16<true>(ubytes(V ? v_lo : k_lo), at, lds);
+    else dma16<true>(ubytes(V ? v_hi : k_hi), at, lds);
   };
   // Each KV tile of the (b, n, kv head) group is written to the cache by exactly
   // one workgroup of that group (query tile t % n_qt of head g*G + (t / n_qt) % G),

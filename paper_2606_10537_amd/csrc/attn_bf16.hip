@@ -23,10 +23,10 @@
 // sweep_pingpong: one workgroup of eight waves whose halves run half a tile apart,
 // held there by barriers; each tile in LDS serves twice the rows (half the
 // traffic from L2), but the start, 8 us, and the end of a workgroup are bare.  The
-// matrix cores are busy 43 % (decode of 8 x 32K) and 47 % (prefill) of the cycles;
-// the waves issue 35 and 39 % of their time, wait 36 and 37 % for an issue slot and 29
-// and 23 % for a barrier, a DMA or LDS data.  By the cycle counters the clock is
-// 2.1 GHz in that decode and 1.6 in that prefill, of 2.4.  Against
+// matrix cores are busy 42 % (decode of 8 x 32K) and 47 % (prefill) of the cycles;
+// the waves issue 34 and 39 % of their time, wait 36 and 39 % for an issue slot and 29
+// and 21 % for a barrier, a DMA or LDS data.  By the cycle counters the clock is
+// 2.2 GHz in that decode and 1.6 in that prefill, of 2.4.  Against
 // one workgroup of eight waves with one barrier a tile (before): prefill of 8 x
 // 32K 14.67 -> 14.05 ms, of 16K 595 -> 539 us, joint pass of 2 x 1156 rows 86 ->
 // 67 us, step of 8 x 32K 142.7 -> 139.7 us.

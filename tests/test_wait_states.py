@@ -61,7 +61,7 @@ def check(lines):
     return bad, dmas
 
 
-def test_checker_sees_each_kind():
+def test_each_rule():
     lds = "global_load_lds_dwordx4 v1, s[4:5]"
     assert check(["v_readfirstlane_b32 s5, v2", "s_mov_b32 m0, s9", "s_nop 3", lds]) == ([], 1)
     assert len(check(["v_readfirstlane_b32 s5, v2", "s_mov_b32 m0, s9", "s_nop 2", lds])[0]) == 1
